@@ -15,6 +15,7 @@
 #include "internal.h"
 #include "kernels.hip"
 #include "solve.hip"
+#include "sweep.h"
 
 namespace wcs {
 const Symbolic &symbolic_of(wcs_symbolic h);
@@ -73,6 +74,7 @@ int32_t solve_step_min_rows()
     const char *e = std::getenv("WCS_SOLVE_STEP_ROWS");
     return e ? std::atoi(e) : 0;
 }
+constexpr int SWEEP_MAX_RHS = 8;             // right-hand sides of the persistent sweeps (k_sweep)
 constexpr int kPartBlocks = 512;             // blocks of the two-pass column reductions
 
 // Leaf fronts whose pivot columns fit in LDS are factored by one persistent
@@ -223,6 +225,119 @@ struct Plan {
     std::vector<int32_t> diag_fronts;             // OP_DIAG tasks (fronts)
     std::vector<int4> step_tasks;                 // OP_STEP tasks (front, i0, j0, flags)
     int32_t nbo = 512;                            // outer block of this plan
+    // persistent sweeps for few right-hand sides (k_sweep): forward tasks, then backward ones
+    std::vector<SweepTask> sw_tasks;
+    std::vector<SweepItem> sw_items;
+    int64_t sw_fwd = 0;
+    bool sw_ok = false;
+
+    // needs the solve schedule (xoff, sbsum_tasks) of every front
+    void build_sweep(const Symbolic &S, const std::vector<std::vector<int32_t>> &bylev)
+    {
+        const int32_t ns = S.ns, H = (int32_t)bylev.size();
+        sw_tasks.clear();
+        sw_items.clear();
+        sw_fwd = 0;
+        // positions of W rows, index lists and partial slots are 32-bit in the tasks
+        sw_ok = ns > 0 && wrows < INT32_MAX && (int64_t)S.rows.size() < INT32_MAX && part_blocks < INT32_MAX / 2;
+        for (int32_t s = 0; s < ns && sw_ok; s++) sw_ok = xoff[s] >= 0;
+        if (!sw_ok) return;
+        auto blocks = [&](int32_t s) { return (pfront[s] + SB - 1) / SB; };
+        auto narrow = [&](int32_t s) { return pfront[s] <= SB; };
+        auto task = [&](int32_t s, int32_t kind, int32_t idx, int32_t r0) {
+            SweepTask t{};
+            t.foff = S.front_off[s];
+            t.xoff = xoff[s];
+            t.rptr = S.rptr[s];
+            t.woff = woff[s];
+            t.m = mfront[s];
+            t.p = pfront[s];
+            t.first = first[s];
+            t.kind = kind;
+            t.idx = idx;
+            t.r0 = r0;
+            return t;
+        };
+        // forward task: with the children's update rows that land in rows [r0, hi)
+        auto forward = [&](int32_t s, SweepTask t, int32_t hi) {
+            t.i0 = (int32_t)sw_items.size();
+            for (int32_t q = child_ptr[s]; q < child_ptr[s + 1]; q++) {
+                int32_t c = child_list[q], pc = pfront[c];
+                const int32_t *rl = S.rel.data() + S.rptr[c] + pc, *re = rl + (mfront[c] - pc);
+                int32_t a0 = (int32_t)(std::lower_bound(rl, re, t.r0) - rl);
+                int32_t a1 = (int32_t)(std::lower_bound(rl, re, hi) - rl);
+                if (a0 == a1) continue;
+                sw_items.push_back({(int32_t)(woff[c] + pc + a0), (int32_t)(S.rptr[c] + pc + a0), a1 - a0, 0});
+            }
+            t.i1 = (int32_t)sw_items.size();
+            sw_tasks.push_back(t);
+        };
+        for (int32_t h = 0; h < H; h++) {
+            int32_t maxb = 0;
+            for (int32_t s : bylev[h])
+                if (!narrow(s)) maxb = std::max(maxb, blocks(s));
+            for (int32_t i = 0; i < 2 * maxb; i++)
+                for (int32_t s : bylev[h])
+                    if (!narrow(s) && i * 32 < pfront[s])
+                        forward(s, task(s, SW_FWD_PIV, i, i * 32), std::min(pfront[s], (i + 1) * 32));
+            for (int32_t s : bylev[h])
+                for (int32_t r0 = pfront[s]; !narrow(s) && r0 < mfront[s]; r0 += SB)
+                    forward(s, task(s, SW_FWD_TILE, 0, r0), std::min(mfront[s], r0 + SB));
+            for (int32_t s : bylev[h])
+                if (narrow(s)) {
+                    forward(s, task(s, SW_FWD_FRONT, 0, 0), std::min(mfront[s], pfront[s] + SW_ROWS));
+                    for (int32_t u = 1; pfront[s] + u * SW_ROWS < mfront[s]; u++) {
+                        SweepTask t = task(s, SW_FWD_ROWS, 0, pfront[s] + u * SW_ROWS);
+                        forward(s, t, std::min(mfront[s], t.r0 + SW_ROWS));
+                    }
+                }
+        }
+        sw_fwd = (int64_t)sw_tasks.size();
+        std::vector<int64_t> slot0((size_t)ns, 0);
+        for (const int4 &q : sbsum_tasks)
+            if (q.y == 0) slot0[q.x] = q.z;
+        // the partial sums of the update rows from chunk q0 on, for column block b
+        auto parts = [&](int32_t s, int32_t b, int32_t q0, bool emit) {
+            int32_t m = mfront[s], p = pfront[s];
+            int32_t nq = m > p ? (m - (p & ~3) + BELOW_ROWS - 1) / BELOW_ROWS : 0;
+            int32_t s0 = (int32_t)(slot0[s] + (int64_t)b * nq);
+            for (int32_t q = q0; q < nq && emit; q++) {
+                SweepTask t = task(s, SW_BWD_PART, b, (p & ~3) + q * BELOW_ROWS);
+                t.i0 = s0 + q;
+                sw_tasks.push_back(t);
+            }
+            return std::make_pair(s0 + std::min(q0, nq), s0 + nq);
+        };
+        for (int32_t h = H; h-- > 0;) {
+            int32_t maxb = 0;
+            for (int32_t s : bylev[h])
+                if (!narrow(s)) maxb = std::max(maxb, blocks(s));
+            for (int32_t d = 0; d < maxb; d++)       // the last blocks first
+                for (int pass = 0; pass < 2; pass++)
+                    for (int32_t s : bylev[h]) {
+                        if (narrow(s) || d >= blocks(s)) continue;
+                        int32_t b = blocks(s) - 1 - d;
+                        auto r = parts(s, b, 0, pass == 0);
+                        if (pass == 0) continue;
+                        for (int32_t i = 2 * b + 1; i >= 2 * b; i--) {
+                            if (i * 32 >= pfront[s]) continue;
+                            SweepTask t = task(s, SW_BWD_COL, i, 0);
+                            t.i0 = r.first;
+                            t.i1 = r.second;
+                            sw_tasks.push_back(t);
+                        }
+                    }
+            for (int32_t s : bylev[h])
+                if (narrow(s)) {
+                    auto r = parts(s, 0, 1, true);
+                    SweepTask t = task(s, SW_BWD_FRONT, 0, 0);
+                    t.i0 = r.first;
+                    t.i1 = r.second;
+                    sw_tasks.push_back(t);
+                }
+        }
+        if ((int64_t)sw_tasks.size() > INT32_MAX / 2 || (int64_t)sw_items.size() > INT32_MAX / 2) sw_ok = false;
+    }
 
     // esz: element size of the fronts; leaf_ok: route leaf fronts that fit in
     // LDS to the persistent leaf kernel
@@ -539,6 +654,7 @@ struct Plan {
                 V.bwd.push_back({s0, d.first, d.second, off, (int64_t)sbwd_tasks.size() - off});
             }
         }
+        build_sweep(S, bylev);
         // SpMV chunks of the pivot-order CSR
         spmv_chunks.clear();
         spmv_long.clear();
@@ -660,6 +776,7 @@ struct Layout {
     size_t pan, upd, ea, flist, dscr, dinv, dscr_off, slist, sfwd, sbelow, sbwd, sasm, part, ztasks;
     size_t sblk, sbsum, xinvt, xoff, xinv, part2, dinvt, altt, alt2, gptr, glist;
     size_t spchunk, splong, sppart, iperm, leafq, leafc, diagf, stept, spgrp, spgit, spglong;
+    size_t swt, swi, swx;
     // LU factors only: the U^T fronts and their diagonal-block scratch, inverses and super-block inverses
     size_t fronts_u = 0, dscr_u = 0, dinv_u = 0, xinv_u = 0;
     size_t total;
@@ -741,6 +858,10 @@ struct Layout {
         leafc = seg(4);
         diagf = seg(std::max<size_t>(1, P.diag_fronts.size()) * 4);
         stept = seg(std::max<size_t>(1, P.step_tasks.size()) * sizeof(int4));
+        swt = seg(P.sw_tasks.size() * sizeof(SweepTask));
+        swi = seg(P.sw_items.size() * sizeof(SweepItem));
+        // exchange arrays (z, w, v, x), then ctl
+        swx = seg(P.sw_ok ? (size_t)4 * n * std::min(k, SWEEP_MAX_RHS) * esz + 16 : 0);
         total = o;
     }
 };
@@ -1332,9 +1453,52 @@ int launch_sweeps(wcs_factor f, int part, int k, hipStream_t st)
     return WCS_OK;
 }
 
+// The sweeps of at most SWEEP_MAX_RHS right-hand sides as one persistent launch (k_sweep)
+template <typename T, int KT>
+int launch_sweep(wcs_factor f, int part, int k, hipStream_t st)
+{
+    const Layout &Lo = f->lay;
+    const Plan &P = f->plan;
+    const bool lu = is_lu(f->prec);
+    SweepArgs<T> a;
+    a.tasks = f->at<SweepTask>(Lo.swt);
+    a.items = f->at<SweepItem>(Lo.swi);
+    a.rel = f->at<int32_t>(Lo.rel);
+    a.rows = f->at<int32_t>(Lo.rows);
+    a.fronts = f->at<T>(Lo.fronts);
+    a.xinv = f->at<T>(Lo.xinv);
+    a.fronts_u = lu ? f->at<T>(Lo.fronts_u) : a.fronts;
+    a.xinv_u = lu ? f->at<T>(Lo.xinv_u) : a.xinv;
+    a.W = f->at<T>(Lo.W);
+    a.Y = f->at<T>(Lo.Y);
+    a.part = f->at<T>(Lo.part2);
+    a.ex = f->at<T>(Lo.swx);
+    a.nk = (int64_t)f->S->n * k;
+    a.ctl = reinterpret_cast<int32_t *>(a.ex + 4 * a.nk);
+    a.k = k;
+    a.part_l = part == WCS_SOLVE_L;
+    a.from_z = part == WCS_SOLVE_FULL;
+    a.t0 = part == WCS_SOLVE_LT ? (int32_t)P.sw_fwd : 0;
+    a.t1 = part == WCS_SOLVE_L ? (int32_t)P.sw_fwd : (int32_t)P.sw_tasks.size();
+    const int64_t wpe = sizeof(T) / 4;
+    const int64_t n0 = 4 * a.nk * wpe + 2, n1 = a.t0 ? 0 : P.wrows * k * wpe;
+    const int64_t n2 = part == WCS_SOLVE_L ? 0 : P.part_blocks * SB * k * wpe;
+    hipLaunchKernelGGL(k_sweep_fill, dim3((unsigned)std::min<int64_t>(grid_for((n0 + n1 + n2) / 4), 8 * f->ncu)),
+                       dim3(256), 0, st, reinterpret_cast<int32_t *>(a.ex), n0, reinterpret_cast<int32_t *>(a.W), n1,
+                       reinterpret_cast<int32_t *>(a.part), n2);
+    hipLaunchKernelGGL((k_sweep<T, KT>), dim3((unsigned)std::min(a.t1 - a.t0, sweep_per_cu<T, KT>() * f->ncu)), dim3(THREADS), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return WCS_OK;
+}
+
 template <typename T>
 int launch_solve_internal(wcs_factor f, int part, int k, hipStream_t st)
 {
+    if (f->plan.sw_ok && k <= SWEEP_MAX_RHS) {
+        if (k == 1) return launch_sweep<T, 1>(f, part, k, st);
+        if (k <= 4) return launch_sweep<T, 4>(f, part, k, st);
+        return launch_sweep<T, 8>(f, part, k, st);
+    }
     if (k <= 4) return launch_sweeps<T, 4>(f, part, k, st);
     if (k <= kt16_max_rhs()) return launch_sweeps<T, 16>(f, part, k, st);
     return launch_sweeps<T, 64>(f, part, k, st);
@@ -1962,6 +2126,8 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
     rc = rc ? rc : upload(f, L.leafq, P.leaf_queue, st);
     rc = rc ? rc : upload(f, L.diagf, P.diag_fronts, st);
     rc = rc ? rc : upload(f, L.stept, P.step_tasks, st);
+    rc = rc ? rc : upload(f, L.swt, P.sw_tasks, st);
+    rc = rc ? rc : upload(f, L.swi, P.sw_items, st);
     std::vector<int32_t> segp = S.seg_ptr.size() >= 2 ? S.seg_ptr : std::vector<int32_t>{0, S.n};
     rc = rc ? rc : upload(f, L.segp, segp, st);
     if (rc == WCS_OK) {

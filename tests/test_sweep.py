@@ -1,0 +1,67 @@
+"""Persistent triangular sweeps (at most 8 right-hand sides) against the oracle.
+
+The cases hold narrow fronts (one pivot block) with more and fewer than 256
+update rows, wide ones with ragged pivot blocks and super-blocks, and roots;
+the column counts are the edges of the kernel's three widths.  A batch of two
+copies gives a forest.  Right-hand sides with NaN (one of them the all-ones
+pattern that marks an empty exchange element) come back as NaN.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import normal_rhs
+from tests.helpers import EPS32, EPS64, factor_tol
+from tests.test_gpu_parity import CASES, dev, prepared
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+from paper_2007_01541_amd import FP32, FP64, SOLVE_FULL, SOLVE_L, SOLVE_LT, Factor, Symbolic  # noqa: E402
+
+
+@pytest.mark.parametrize("kind,leaf,coords", CASES)
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_sweeps_match_oracle(kind, leaf, coords, prec):
+    m, sym, orc = prepared(kind, leaf, coords)
+    n = m["n"]
+    p = np.diff(sym.export()["relaxed_ptr"])
+    print(f"case {kind} prec={prec} n={n} fronts {p.size} largest {p.max()}", flush=True)
+    f = Factor(sym, prec, max_nrhs=8)
+    f.numeric(dev(m["values"]))
+    B = normal_rhs(n, 8, 91)
+    tol = factor_tol(m, int(orc.colcount.max()), EPS64 if prec == FP64 else EPS32)
+    for part in (SOLVE_FULL, SOLVE_L, SOLVE_LT):
+        Xo = orc.solve(B, part)
+        for k in (1, 2, 4, 5, 8):
+            b = dev(B[:, :k])
+            X = f.solve(b, part)
+            assert np.abs(X.cpu().numpy() - Xo[:, :k]).max() <= tol * np.abs(Xo).max(), (part, k)
+            for _ in range(3):
+                assert torch.equal(f.solve(b, part), X), (part, k)
+
+
+def test_sweeps_of_a_forest():
+    m, sym, orc = prepared("g6alg", 32, True)
+    n = m["n"]
+    both = Symbolic.batch([sym, sym])
+    f = Factor(both, FP64, max_nrhs=3)
+    v = dev(m["values"])
+    f.numeric(torch.cat([v, 2.0 * v]))
+    B = normal_rhs(2 * n, 3, 92)
+    X = f.solve(dev(B)).cpu().numpy()
+    tol = factor_tol(m, int(orc.colcount.max()), EPS64)
+    for b, scale in ((0, 1.0), (1, 0.5)):
+        Xo = scale * orc.solve(B[b * n:(b + 1) * n])
+        assert np.abs(X[b * n:(b + 1) * n] - Xo).max() <= tol * np.abs(Xo).max()
+
+
+@pytest.mark.parametrize("bits", [0x7FF8000000000000, 0xFFFFFFFFFFFFFFFF])
+def test_sweeps_pass_nan_on(bits):
+    m, sym, _ = prepared("small")
+    f = Factor(sym, FP64, max_nrhs=2)
+    f.numeric(dev(m["values"]))
+    B = normal_rhs(m["n"], 2, 93)
+    B[:, 1] = np.full(m["n"], bits, np.uint64).view(np.float64)
+    X = f.solve(dev(B)).cpu().numpy()
+    assert np.isfinite(X[:, 0]).all() and np.isnan(X[:, 1]).all()
