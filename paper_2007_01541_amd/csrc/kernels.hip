@@ -29,11 +29,11 @@ constexpr int ZCOLS = 16;
 template <typename T>
 __global__ void k_zero_lower(const int2 *__restrict__ tasks, const int64_t *__restrict__ front_off,
                              const int32_t *__restrict__ mfront, const int32_t *__restrict__ pfront,
-                             T *__restrict__ fronts)
+                             T *__restrict__ fronts, int64_t udelta)
 {
     int2 t = tasks[blockIdx.x];
     int m = mfront[t.x], ld = front_ld(m);
-    T *F = fronts + front_off[t.x];
+    T *F = fronts + blockIdx.y * udelta + front_off[t.x];
     int c1 = min(t.y + ZCOLS, pfront[t.x]);
     // 16-byte stores over the aligned groups of VEC rows that hold rows >= c (the
     // column starts are 32-byte aligned; a group may reach into the upper
@@ -102,8 +102,9 @@ __global__ __launch_bounds__(256) void k_extend_add(const int2 *__restrict__ tas
                                                     const int32_t *__restrict__ mfront, const int32_t *__restrict__ pfront,
                                                     const int32_t *__restrict__ sparent, const int64_t *__restrict__ rptr,
                                                     const int32_t *__restrict__ rel, const int32_t *__restrict__ split,
-                                                    T *__restrict__ fronts)
+                                                    T *__restrict__ fronts, int64_t udelta)
 {
+    fronts += blockIdx.y * udelta;
     int2 t = tasks[blockIdx.x];
     int c = t.x;
     int mc = mfront[c], pc = pfront[c];

@@ -1099,14 +1099,14 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
     const bool lu = is_lu(f->prec);
     T *fronts = f->at<T>(Lo.fronts);
     T *fronts_u = lu ? f->at<T>(Lo.fronts_u) : nullptr;
-    const int nbuf = lu ? 2 : 1;
-    auto buf = [&](int b) { return b ? fronts_u : fronts; };
+    // LU: every launch on the fronts runs on both buffers (grid y)
+    const unsigned nbuf = lu ? 2 : 1;
+    const int64_t udelta = lu ? (int64_t)(fronts_u - fronts) : 0;
     hipLaunchKernelGGL(k_fill<int32_t>, dim3(1), dim3(64), 0, st, f->at<int32_t>(Lo.bad), (int64_t)1, INT32_MAX);
     PROF_BEGIN(KC_FILL);
-    for (int b = 0; b < nbuf; b++)
-        hipLaunchKernelGGL(k_zero_lower<T>, dim3((unsigned)std::min<int64_t>(P.zero_tasks.size(), 1 << 30)), dim3(256),
-                           0, st, f->at<int2>(Lo.ztasks), f->at<int64_t>(Lo.front_off), f->at<int32_t>(Lo.mfront),
-                           f->at<int32_t>(Lo.pfront), buf(b));
+    hipLaunchKernelGGL(k_zero_lower<T>, dim3((unsigned)std::min<int64_t>(P.zero_tasks.size(), 1 << 30), nbuf), dim3(256),
+                       0, st, f->at<int2>(Lo.ztasks), f->at<int64_t>(Lo.front_off), f->at<int32_t>(Lo.mfront),
+                       f->at<int32_t>(Lo.pfront), fronts, udelta);
     PROF_END(KC_FILL);
     PROF_BEGIN(KC_SCATTER);
     if constexpr (sizeof(T) == 8) {
@@ -1147,9 +1147,8 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
     auto extend_add = [&](const std::vector<std::pair<int64_t, int64_t>> &rounds, bool pre) -> int {
         for (auto &r : rounds) {
             PROF_BEGIN(KC_EXTEND_ADD);
-            for (int b = 0; b < nbuf; b++)
-                hipLaunchKernelGGL(k_extend_add<T>, dim3((unsigned)r.second), dim3(256), 0, st, ea + r.first, fo, mf,
-                                   pf, sp, rp, rl, pre ? esp : nullptr, buf(b));
+            hipLaunchKernelGGL(k_extend_add<T>, dim3((unsigned)r.second, nbuf), dim3(256), 0, st, ea + r.first, fo, mf,
+                               pf, sp, rp, rl, pre ? esp : nullptr, fronts, udelta);
             PROF_END(KC_EXTEND_ADD);
             if (prof)
                 for (int64_t t = r.first; t < r.first + r.second; t++) {
@@ -1223,26 +1222,23 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
                     us = side;
                 }
                 PROF_BEGIN(KC_UPDATE);
-                for (int b = 0; b < nbuf; b++) {
-                    // LU: the L fronts take B from the U^T fronts and the other way round
-                    T *cf = buf(b);
-                    const int64_t bd = lu ? (int64_t)(buf(1 - b) - cf) : 0;
-                    if (small)
-                        hipLaunchKernelGGL((k_update<T, 64>), dim3(grid), dim3(64), 0, us, upd + off, (int)cnt, op.ka,
-                                           op.kw, cf, bd);
-                    else if (L.upd_var == WCS_UPD_STREAM128)
-                        hipLaunchKernelGGL((k_update_dma<T, 4>), dim3(grid), dim3(256), 0, us, upd + off, (int)cnt,
-                                           op.ka, op.kw, cf, bd);
-                    else if (L.upd_var == WCS_UPD_STREAM128_3)
-                        hipLaunchKernelGGL((k_update_dma<T, 3>), dim3(grid), dim3(256), 0, us, upd + off, (int)cnt,
-                                           op.ka, op.kw, cf, bd);
-                    else if (L.upd_var == WCS_UPD_STREAM128_K32)
-                        hipLaunchKernelGGL((k_update_dma<T, 2, 2 * DmaCfg<T>::KC>), dim3(grid), dim3(256), 0, us,
-                                           upd + off, (int)cnt, op.ka, op.kw, cf, bd);
-                    else
-                        hipLaunchKernelGGL((k_update<T, UT>), dim3(grid), dim3(UT * UT / 64), 0, us,
-                                           upd + off, (int)cnt, op.ka, op.kw, cf, bd);
-                }
+                // LU: the L fronts take B from the U^T fronts and the other way round
+                const dim3 ug(grid, nbuf);
+                if (small)
+                    hipLaunchKernelGGL((k_update<T, 64>), ug, dim3(64), 0, us, upd + off, (int)cnt, op.ka, op.kw, fronts,
+                                       udelta);
+                else if (L.upd_var == WCS_UPD_STREAM128)
+                    hipLaunchKernelGGL((k_update_dma<T, 4>), ug, dim3(256), 0, us, upd + off, (int)cnt, op.ka, op.kw,
+                                       fronts, udelta);
+                else if (L.upd_var == WCS_UPD_STREAM128_3)
+                    hipLaunchKernelGGL((k_update_dma<T, 3>), ug, dim3(256), 0, us, upd + off, (int)cnt, op.ka, op.kw,
+                                       fronts, udelta);
+                else if (L.upd_var == WCS_UPD_STREAM128_K32)
+                    hipLaunchKernelGGL((k_update_dma<T, 2, 2 * DmaCfg<T>::KC>), ug, dim3(256), 0, us, upd + off,
+                                       (int)cnt, op.ka, op.kw, fronts, udelta);
+                else
+                    hipLaunchKernelGGL((k_update<T, UT>), ug, dim3(UT * UT / 64), 0, us, upd + off, (int)cnt, op.ka,
+                                       op.kw, fronts, udelta);
                 PROF_END(KC_UPDATE);
                 if (us != st) {
                     HIP_TRY(hipEventRecord(f->ev_side, side));
@@ -1320,15 +1316,15 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
                 HIP_TRY(hipStreamWaitEvent(aux, f->ev_main, 0));
             }
             PROF_BEGIN(KC_FILL);
-            for (int b = 0; b < nbuf; b++)
+            for (unsigned b = 0; b < nbuf; b++)
                 hipLaunchKernelGGL(k_diag_inv<T>, dim3((unsigned)L.dinv_cnt), dim3(64), 0, aux,
                                    f->at<int2>(Lo.dinvt) + L.dinv_off, dso, b ? f->at<T>(Lo.dscr_u) : dscr,
-                                   b ? f->at<T>(Lo.dinv_u) : dinv, fo, mf, pf, buf(b));
+                                   b ? f->at<T>(Lo.dinv_u) : dinv, fo, mf, pf, b ? fronts_u : fronts);
             const std::pair<int64_t, int64_t> &xt = L.sv.xinv;
-            for (int b = 0; b < nbuf && xt.second; b++)
+            for (unsigned b = 0; b < nbuf && xt.second; b++)
                 hipLaunchKernelGGL(k_build_xinv<T>, dim3((unsigned)xt.second), dim3(THREADS), 0, aux,
                                    f->at<int4>(Lo.xinvt) + xt.first, fo, mf, pf, dso, f->at<int64_t>(Lo.xoff),
-                                   buf(b), b ? f->at<T>(Lo.dinv_u) : dinv,
+                                   b ? fronts_u : fronts, b ? f->at<T>(Lo.dinv_u) : dinv,
                                    b ? f->at<T>(Lo.xinv_u) : f->at<T>(Lo.xinv));
             PROF_END(KC_FILL);
             // read the block, write its inverse and the lower half of its place

@@ -589,11 +589,17 @@ __device__ __forceinline__ void update_tile_dma(const UpdTask t, int ka, int kw,
 // The trailing-update kernels: workgroup b takes tasks b, b + grid, ... (a
 // launch may use fewer workgroups than tasks: the look-ahead updates on the
 // side stream do, so that the panel-step kernels on the main stream always
-// find room on the compute units).
+// find room on the compute units).  LU: grid y = 1 updates the U^T fronts,
+// bdelta elements further on, with B from the L fronts (one launch for both
+// instead of two: LU at N = 65,536 25.2 -> 21.0 ms with the extend-adds merged likewise).
 template <typename T, int TW>
 __global__ __launch_bounds__(TW * TW / 64, 2) void k_update(const UpdTask *__restrict__ tasks, int ntask, int ka,
                                                             int kw, T *__restrict__ fronts, int64_t bdelta)
 {
+    if (blockIdx.y) {
+        fronts += bdelta;
+        bdelta = -bdelta;
+    }
     for (int i = blockIdx.x; i < ntask; i += gridDim.x) {
         if (i != (int)blockIdx.x) __syncthreads();   // the previous tile's LDS reads are done
         update_tile<T, TW>(tasks[i], ka, kw, fronts, bdelta);
@@ -604,6 +610,10 @@ template <typename T, int NS, int KC = DmaCfg<T>::KC>
 __global__ __launch_bounds__(256, (NS == 3 && sizeof(T) == 4) ? 3 : 2) void k_update_dma(
     const UpdTask *__restrict__ tasks, int ntask, int ka, int kw, T *__restrict__ fronts, int64_t bdelta)
 {
+    if (blockIdx.y) {
+        fronts += bdelta;
+        bdelta = -bdelta;
+    }
     for (int i = blockIdx.x; i < ntask; i += gridDim.x) {
         if (i != (int)blockIdx.x) __syncthreads();   // the previous tile's LDS reads are done
         update_tile_dma<T, NS, KC>(tasks[i], ka, kw, fronts, bdelta);
