@@ -86,10 +86,6 @@ bool leaf_kernel_enabled()
     return e ? std::atoi(e) != 0 : true;
 }
 
-// Cholesky fronts with at least this many pivots are factored by the fused
-// panel steps (k_diag_factor + k_step) instead of the panel kernel and a
-// separate update of the outer block's later columns (environment
-// WCS_STEP_MIN_COLS; read when a plan is built).  Same factor bit for bit.
 // Workgroups of a look-ahead trailing update on the side stream, as a
 // multiple of the compute units (environment WCS_SIDE_GRID, workgroups per
 // compute unit in quarters; default 0 = one workgroup per tile): the tiles
@@ -118,22 +114,33 @@ int kt16_max_rhs()
 // Fronts with at least this many pivots are factored as late as their
 // parent allows (one level below it) instead of at their height in the
 // assembly tree (environment WCS_LATE_MIN_PIVOTS, read when a factor is
-// created; default 1024, 0 = off): a large front off the longest path of the
+// created; default 256, 0 = off): a front off the longest path of the
 // tree then shares the launches of a level above with the fronts it is
 // independent of, instead of lengthening the chain of its own level.
-// Measured at N = 2^18 (alternating runs): FP32 factor 43.8 ms at their
-// heights, 43.5 with 2048, 43.0 with 1024, 43.1 with 512; FP64 78.5, 78.1,
-// 77.8, 77.7 ms; one FP32 solve 8.64 -> 8.33 ms with 1024.
+// Measured (factor + solve) with 1024, 512, 256 and 128: N = 65,536 FP64
+// 11.20, 11.04, 10.79 and 10.76 ms; a batch of 32 in FP32 11.13, 11.13,
+// 11.10 and 11.20; N = 262,144 with 64 right-hand sides, FP32 65.5, 65.5,
+// 65.4 and 65.2, FP64 93.1, 93.1, 93.1 and 92.7.
 int32_t late_min_pivots()
 {
     const char *e = std::getenv("WCS_LATE_MIN_PIVOTS");
-    return e ? std::atoi(e) : 1024;
+    return e ? std::atoi(e) : 256;
 }
 
+// Cholesky fronts with at least this many pivots are factored by the fused
+// panel steps (k_diag_factor + k_step) instead of the panel kernel and a
+// separate update of the outer block's later columns (environment
+// WCS_STEP_MIN_COLS; read when a plan is built).  Same factor bit for bit.
+// Default: every front of more than one panel; a step is one launch of 23-30
+// us per panel where panel and update take 40 us and more, and wide levels
+// are indifferent.  Measured (factor + solve) with 1024 and 65: N = 1,024
+// FP64 1.02 and 0.95 ms; N = 4,096 FP32 2.00 and 1.83; N = 11,470 FP64 3.52
+// and 3.23; N = 65,536 FP64 12.0 and 11.2; N = 262,144 with 64 right-hand
+// sides, FP32 65.4 and 65.5, FP64 93.0 and 93.1.
 int32_t step_min_cols()
 {
     const char *e = std::getenv("WCS_STEP_MIN_COLS");
-    return e ? std::atoi(e) : 1024;
+    return e ? std::atoi(e) : NB + 1;
 }
 
 // Static schedule derived from the symbolic structure only.  Inside every
