@@ -905,54 +905,96 @@ __global__ __launch_bounds__(THREADS, 2) void k_step(const int4 *__restrict__ ta
     if (w & STEP_COPY) move_deferred<T>(F, ld, m, i0, i0 + NB, K0, k0, Lt);
 }
 
+// The inverses that the solves use, level by level, off the panel chain
+// (beside the levels above; the last level's are what a caller waits for).
+// Buffer b = grid y (LU: 1 is the U^T factor).
+constexpr int XS = 4 * NB;      // super-block of the solves: X_S = L_SS^-1 is XS x XS, column-major
+template <typename T> struct InvArgs {
+    const int64_t *dscr_off, *front_off, *xoff;   // xoff: per front, offset of its super-block inverses (-1: none)
+    const int32_t *mfront, *pfront;
+    T *fronts[2], *dscr[2], *dinv[2], *xinv[2];
+};
+
 // Every factored NB x NB diagonal block of a level's fronts (task = (front,
 // block)), from its copy in dscr: copied into the lower triangle of its place
 // in the front, and inverted in FP64 and rounded to T into dinv (column major,
-// same offsets).  One wave per block; lane c forms column c of L^-1 by forward
-// substitution, right-looking (15 and more independent updates per step).
-// The triangular solves use these; nothing in the factorization reads them,
-// so each level's blocks are handled beside the levels above it, off the
-// panel chain.
+// same offsets) and into its place in the super-block inverse.  Latency-bound:
+// wave w inverts the 16 x 16 diagonal sub-block w by forward substitution (a
+// column per lane), then the blocks below follow by their distance d from the
+// diagonal, X_ij = -X_ii sum_q L_iq X_qj, one block per wave and d, as FP64
+// matrix-core products whose accumulator is the next product's operand.  X
+// shares L's array (33 KB of LDS, four workgroups per compute unit): its
+// diagonal sub-blocks replace L's, the blocks below them go to the transposed
+// positions.  (One wave substituting all 64 columns took 22-27 us per launch
+// on the narrow levels, this form 8.)
 template <typename T>
-__global__ __launch_bounds__(64) void k_diag_inv(const int2 *__restrict__ tasks,
-                                                 const int64_t *__restrict__ dscr_off, const T *__restrict__ dscr,
-                                                 T *__restrict__ dinv, const int64_t *__restrict__ front_off,
-                                                 const int32_t *__restrict__ mfront,
-                                                 const int32_t *__restrict__ pfront, T *__restrict__ fronts)
+__global__ __launch_bounds__(THREADS) void k_diag_inv(const int2 *__restrict__ tasks, InvArgs<T> a)
 {
-    __shared__ double L[NB][NB + 1];   // column-major: L[c][r] = L(r, c)
-    int2 t = tasks[blockIdx.x];
-    int64_t o = dscr_off[t.x] + (int64_t)t.y * NB * NB;
-    const T *D = dscr + o;
-    const int c = threadIdx.x;
+    typedef Mfma<double>::V V;
+    __shared__ double L[NB][NB + 1];     // column-major: L[c][r] = L(r, c)
+    const int2 t = tasks[blockIdx.x];
+    const int f = t.x, b = blockIdx.y;
+    const int64_t o = a.dscr_off[f] + (int64_t)t.y * NB * NB, xo = a.xoff[f];
+    const T *D = a.dscr[b] + o;
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, kq = lane / 16, ln = lane % 16;
+    const int k0 = t.y * NB, nb = min(NB, a.pfront[f] - k0), ld = front_ld(a.mfront[f]);
     {
-        // lane c loads row c of every column (all loads in flight)
-        T v[NB];
+        // thread (wave, lane): row lane of columns wave + 4 i, all loads in flight
+        T v[NB / 4];
+        T *F = a.fronts[b] + a.front_off[f] + (int64_t)k0 * ld + k0;
 #pragma unroll
-        for (int j = 0; j < NB; j++) v[j] = D[j * NB + c];
-        const int k0 = t.y * NB, nb = min(NB, pfront[t.x] - k0), ld = front_ld(mfront[t.x]);
-        T *F = fronts + front_off[t.x] + (int64_t)k0 * ld + k0;
+        for (int i = 0; i < NB / 4; i++) v[i] = D[(wave + 4 * i) * NB + lane];
 #pragma unroll
-        for (int j = 0; j < NB; j++)
-            if (c < nb && c >= j) F[(int64_t)j * ld + c] = v[j];
-#pragma unroll
-        for (int j = 0; j < NB; j++) L[j][c] = (double)v[j];
+        for (int i = 0; i < NB / 4; i++) {
+            const int c = wave + 4 * i;
+            if (lane < nb && lane >= c) F[(int64_t)c * ld + lane] = v[i];
+            L[c][lane] = (double)v[i];
+        }
     }
     __syncthreads();
-    double y[NB];
+    if (lane < 16) {
+        const int kb = 16 * wave;
+        double y[16], rd[16];
 #pragma unroll
-    for (int r = 0; r < NB; r++) y[r] = (r == c) ? 1.0 : 0.0;
+        for (int r = 0; r < 16; r++) {
+            y[r] = r == lane ? 1.0 : 0.0;
+            rd[r] = 1.0 / L[kb + r][kb + r];
+        }
 #pragma unroll
-    for (int r = 0; r < NB; r++) {
-        y[r] = y[r] / L[r][r];
+        for (int r = 0; r < 16; r++) {
+            y[r] *= rd[r];
 #pragma unroll
-        for (int q = r + 1; q < NB; q++) y[q] -= L[r][q] * y[r];
+            for (int q = r + 1; q < 16; q++) y[q] -= L[kb + r][kb + q] * y[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) L[kb + lane][kb + r] = y[r];
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < NB; r++) L[c][r] = y[r];
-    __syncthreads();
-    for (int i = c; i < NB * NB; i += 64) dinv[o + i] = (T)L[i / NB][i % NB];
+    for (int d = 1; d < 4; d++) {
+        if (wave + d < 4) {
+            const int jb = 16 * wave, ib = jb + 16 * d;
+            V s = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < d; q++)
+                s = mm16<double>(s, [&](int r, int k) { return L[jb + 16 * q + k][ib + r]; },
+                                 [&](int k, int n) { return q == 0 ? L[jb + n][jb + k] : L[jb + 16 * q + k][jb + n]; });
+            // element e of s is row 4 e + kq of column ln: the B operand of step e
+#pragma unroll
+            for (int e = 0; e < 4; e++) x = Mfma<double>::mma(-L[ib + 4 * e + kq][ib + ln], s[e], x);
+#pragma unroll
+            for (int e = 0; e < 4; e++) L[ib + Mfma<double>::row(kq, e)][jb + ln] = x[e];
+        }
+        __syncthreads();
+    }
+    T *XS_ = xo >= 0 ? a.xinv[b] + xo + (int64_t)(t.y / 4) * XS * XS + (int64_t)(t.y % 4 * NB) * XS + t.y % 4 * NB : nullptr;
+#pragma unroll
+    for (int i = 0; i < NB / 4; i++) {
+        const int c = wave + 4 * i;
+        const T v = lane / 16 == c / 16 ? (T)L[c][lane] : lane > c ? (T)L[lane][c] : (T)0;
+        a.dinv[b][o + c * NB + lane] = v;
+        if (XS_) XS_[(int64_t)c * XS + lane] = lane < nb && c < nb ? v : (T)0;
+    }
 }
 
 // ---------------------------------------------------------------- leaf fronts

@@ -607,7 +607,8 @@ struct Plan {
                 xelems += (int64_t)(nsup - 1) * SS * SS + (int64_t)nb_last * SB * SS;
                 for (int32_t si = 0; si < nsup; si++) {
                     int32_t nb = (std::min(pfront[s], (si + 1) * SS) - si * SS + SB - 1) / SB;
-                    for (int32_t jb = 0; jb < nb; jb++) xinv_tasks.push_back(make_int4(s, si, jb, 0));
+                    for (int32_t jb = 0; jb + 1 < nb; jb++)      // the last column block has nothing below its own
+                        for (int32_t q = 0; q < SB / 16; q++) xinv_tasks.push_back(make_int4(s, si, jb, q));
                 }
             }
             V.xinv.second = (int64_t)xinv_tasks.size() - V.xinv.first;
@@ -1323,16 +1324,14 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
                 HIP_TRY(hipStreamWaitEvent(aux, f->ev_main, 0));
             }
             PROF_BEGIN(KC_FILL);
-            for (unsigned b = 0; b < nbuf; b++)
-                hipLaunchKernelGGL(k_diag_inv<T>, dim3((unsigned)L.dinv_cnt), dim3(64), 0, aux,
-                                   f->at<int2>(Lo.dinvt) + L.dinv_off, dso, b ? f->at<T>(Lo.dscr_u) : dscr,
-                                   b ? f->at<T>(Lo.dinv_u) : dinv, fo, mf, pf, b ? fronts_u : fronts);
+            const InvArgs<T> ia{dso, fo, f->at<int64_t>(Lo.xoff), mf, pf, {fronts, fronts_u}, {dscr, f->at<T>(Lo.dscr_u)},
+                                {dinv, f->at<T>(Lo.dinv_u)}, {f->at<T>(Lo.xinv), f->at<T>(Lo.xinv_u)}};
+            hipLaunchKernelGGL(k_diag_inv<T>, dim3((unsigned)L.dinv_cnt, nbuf), dim3(THREADS), 0, aux,
+                               f->at<int2>(Lo.dinvt) + L.dinv_off, ia);
             const std::pair<int64_t, int64_t> &xt = L.sv.xinv;
-            for (unsigned b = 0; b < nbuf && xt.second; b++)
-                hipLaunchKernelGGL(k_build_xinv<T>, dim3((unsigned)xt.second), dim3(THREADS), 0, aux,
-                                   f->at<int4>(Lo.xinvt) + xt.first, fo, mf, pf, dso, f->at<int64_t>(Lo.xoff),
-                                   b ? fronts_u : fronts, b ? f->at<T>(Lo.dinv_u) : dinv,
-                                   b ? f->at<T>(Lo.xinv_u) : f->at<T>(Lo.xinv));
+            if (xt.second)
+                hipLaunchKernelGGL(k_build_xinv<T>, dim3((unsigned)xt.second, nbuf), dim3(THREADS), 0, aux,
+                                   f->at<int4>(Lo.xinvt) + xt.first, ia);
             PROF_END(KC_FILL);
             // read the block, write its inverse and the lower half of its place
             if (prof) prof->bytes[KC_FILL] += (double)L.dinv_cnt * NB * NB * esz * 2.5 * nbuf;

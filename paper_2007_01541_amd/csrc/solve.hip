@@ -1564,69 +1564,68 @@ __global__ void k_apply_gather(const int64_t *__restrict__ gptr, const int64_t *
     }
 }
 
-// task = (front, super-block index si, column block jb): X_jj = L_jj^-1 (the
-// stored 64-block inverse), then for i > j: X_ij = -L_ii^-1 sum_{j <= q < i} L_iq X_qj.
-// Rows and columns past the end of the super-block are zero.
+// The blocks of the super-block inverses below their diagonal blocks (which
+// k_diag_inv has put in place).  task = (front, super-block index si, column
+// block jb, 16-column strip): for i > j, X_ij = -L_ii^-1 sum_{j <= q < i} L_iq X_qj,
+// wave w forming 16 rows of each product.  A chain of up to nine products and
+// bound by latency: a strip of 16 columns keeps a product at 16 matrix-core
+// instructions per wave (64 columns: 64), and the operands come straight from
+// memory into registers, all of a block row's in flight at once.  (Whole 64-column
+// blocks with both operands staged through LDS: 82-90 us for one super-block
+// of four blocks, this form 10-13.)  Rows past the end of the pivots are zero.
 template <typename T>
-__global__ __launch_bounds__(THREADS) void k_build_xinv(const int4 *__restrict__ tasks, const int64_t *__restrict__ front_off,
-                                                        const int32_t *__restrict__ mfront,
-                                                        const int32_t *__restrict__ pfront,
-                                                        const int64_t *__restrict__ dscr_off,
-                                                        const int64_t *__restrict__ xoff, const T *__restrict__ fronts,
-                                                        const T *__restrict__ dinv, T *__restrict__ xinv)
+__global__ __launch_bounds__(THREADS) void k_build_xinv(const int4 *__restrict__ tasks, InvArgs<T> a)
 {
-    __shared__ T D[SB][SB + 1];
-    __shared__ T S[SB][64];
-    int4 t = tasks[blockIdx.x];
-    int f = t.x, s0 = t.y * SS, jb = t.z;
-    int m = mfront[f], p = pfront[f], ld = front_ld(m);
-    int s1 = min(p, s0 + SS);
-    int nblk = (s1 - s0 + SB - 1) / SB;
-    int j0 = s0 + jb * SB, nj = min(SB, s1 - j0);
-    const T *L = fronts + front_off[f];
-    T *X = xinv + xoff[f] + (int64_t)t.y * SS * SS;
-    auto Xat = [&](int ib, int r, int c) -> T & { return X[(int64_t)(jb * SB + c) * SS + ib * SB + r]; };
-    // X_jj: the stored inverse of block j (column-major 64 x 64, identity-padded)
-    const T *Dj = dinv + dscr_off[f] + (int64_t)(j0 / SB) * SB * SB;
-    for (int e = threadIdx.x; e < SB * SB; e += THREADS) {
-        int c = e / SB, r = e % SB;
-        Xat(jb, r, c) = (r < nj && c < nj) ? Dj[e] : (T)0;
+    static_assert(SS == XS, "super-blocks of the solves and of their inverses");
+    typedef typename Mfma<T>::V V;
+    __shared__ T Xs[4][SB][17];     // the strip's X_qj, q = j ..
+    __shared__ T Ts[SB][17];        // sum_q L_iq X_qj
+    const int4 t = tasks[blockIdx.x];
+    const int f = t.x, jb = t.z, b = blockIdx.y, s0 = t.y * SS;
+    const int m = a.mfront[f], p = a.pfront[f], ld = front_ld(m);
+    const int nblk = (min(p, s0 + SS) - s0 + SB - 1) / SB;
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, kq = lane / 16, ln = lane % 16;
+    const T *L = a.fronts[b] + a.front_off[f] + (int64_t)s0 * ld + s0;
+    const T *Di = a.dinv[b] + a.dscr_off[f] + (int64_t)(s0 / SB) * SB * SB;
+    T *X = a.xinv[b] + a.xoff[f] + (int64_t)t.y * SS * SS;
+    const int c0 = jb * SB + t.w * 16;      // the strip's first column in the super-block
+    for (int e = tid; e < SB * 16; e += THREADS) {
+        const int c = e / SB, r = e % SB;
+        Xs[0][r][c] = X[(int64_t)(c0 + c) * SS + jb * SB + r];
     }
-    for (int ib = jb + 1; ib < nblk; ib++) {
-        int i0 = s0 + ib * SB, ni = min(SB, s1 - i0);
-        BlkAcc<T, 64> acc;
-        acc.zero();
-        // T_i = sum_q L_iq X_qj
-        for (int qb = jb; qb < ib; qb++) {
-            int q0 = s0 + qb * SB, nq = min(SB, s1 - q0);
-            __syncthreads();
-            for (int e = threadIdx.x; e < SB * SB; e += THREADS) {
-                int q = e / SB, i = e % SB;            // L(i0 + i, q0 + q) applied to X row q for output row i
-                D[q][i] = (i < ni && q < nq) ? L[(int64_t)(q0 + q) * ld + i0 + i] : (T)0;
-            }
-            for (int e = threadIdx.x; e < SB * 64; e += THREADS) {
-                int q = e / 64, c = e % 64;
-                S[q][c] = Xat(qb, q, c);
-            }
-            __syncthreads();
-            acc.add(D, S);
+    __syncthreads();
+    const int row = 16 * wave + ln;         // this lane's operand row of every product
+    static_for<1, 4, 1>([&](auto dd) {
+        constexpr int d = decltype(dd)::value;      // block row i = j + d
+        const int ib = jb + d;
+        if (ib >= nblk) return;
+        const bool rok = s0 + ib * SB + row < p;
+        T la[d][16], da[16];
+#pragma unroll
+        for (int q = 0; q < d; q++)
+#pragma unroll
+            for (int st = 0; st < 16; st++)
+                la[q][st] = rok ? L[(int64_t)((jb + q) * SB + 4 * st + kq) * ld + ib * SB + row] : (T)0;
+#pragma unroll
+        for (int st = 0; st < 16; st++) da[st] = Di[(int64_t)ib * SB * SB + (4 * st + kq) * SB + row];
+        V s = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < d; q++)
+#pragma unroll
+            for (int st = 0; st < 16; st++) s = Mfma<T>::mma(la[q][st], Xs[q][4 * st + kq][ln], s);
+#pragma unroll
+        for (int e = 0; e < 4; e++) Ts[16 * wave + Mfma<T>::row(kq, e)][ln] = s[e];
+        __syncthreads();
+#pragma unroll
+        for (int st = 0; st < 16; st++) x = Mfma<T>::mma(-da[st], Ts[4 * st + kq][ln], x);
+#pragma unroll
+        for (int e = 0; e < 4; e++) Xs[d][16 * wave + Mfma<T>::row(kq, e)][ln] = x[e];
+        __syncthreads();
+        for (int e = tid; e < SB * 16; e += THREADS) {
+            const int c = e / SB, r = e % SB;
+            X[(int64_t)(c0 + c) * SS + ib * SB + r] = Xs[d][r][c];
         }
-        __syncthreads();
-        acc.store(SB, 64, 0, [&](int r, int c, T val) { S[r][c] = val; });
-        // X_ij = -L_ii^-1 T_i
-        const T *Di = dinv + dscr_off[f] + (int64_t)(i0 / SB) * SB * SB;
-        for (int e = threadIdx.x; e < SB * SB; e += THREADS) {
-            int c = e / SB, r = e % SB;                 // Linv(r, c) applied to T row c for output row r
-            D[c][r] = Di[e];
-        }
-        __syncthreads();
-        BlkAcc<T, 64> res;
-        res.zero();
-        res.add(D, S);
-        __syncthreads();
-        res.store(SB, 64, 0, [&](int r, int c, T val) { Xat(ib, r, c) = (r < ni && c < nj) ? -val : (T)0; });
-        __syncthreads();
-    }
+    });
 }
 
 }  // namespace dev
