@@ -211,6 +211,10 @@ struct Plan {
     int64_t part_blocks = 0;                      // SB x k partial blocks of the split update-row sums
     std::vector<int64_t> xoff;                    // per front: offset of its super-block inverses (-1: none)
     std::vector<int2> alt_tasks, al_tasks;        // products with the factor: (front, column block) / (front, row tile)
+    // al_tasks: tiles of more than APPLY_STRIP_K pivot columns first, then (up
+    // to al_long) those of more than APPLY_WAVE_K
+    int64_t al_strip = 0, al_long = 0;
+    std::vector<int32_t> glong;                   // rows held by more than GATHER_LONG fronts
     std::vector<int64_t> gptr, glist;             // rows of the L product: W rows holding each row, fronts ascending
     int64_t xelems = 0;
     // SpMV work items: (row, first entry, end entry within the row, partial
@@ -749,14 +753,26 @@ struct Plan {
         // products with the factor
         alt_tasks.clear();
         al_tasks.clear();
-        for (int32_t s = 0; s < ns; s++) {
-            for (int32_t b = 0; b < (pfront[s] + SB - 1) / SB; b++) alt_tasks.push_back(make_int2(s, b));
-            for (int32_t t = 0; t < (mfront[s] + SB - 1) / SB; t++) al_tasks.push_back(make_int2(s, t));
+        al_strip = al_long = 0;
+        for (int pass = 0; pass < 3; pass++) {
+            for (int32_t s = 0; s < ns; s++)
+                for (int32_t t = 0; t < (mfront[s] + SB - 1) / SB; t++) {
+                    const int32_t K = std::min(pfront[s], (t + 1) * SB);
+                    if ((K > APPLY_STRIP_K ? 0 : K > APPLY_WAVE_K ? 1 : 2) == pass) al_tasks.push_back(make_int2(s, t));
+                }
+            if (pass == 0) al_strip = (int64_t)al_tasks.size();
+            if (pass == 1) al_long = (int64_t)al_tasks.size();
         }
+        for (int32_t s = 0; s < ns; s++)
+            for (int32_t b = 0; b < (pfront[s] + SB - 1) / SB; b++) alt_tasks.push_back(make_int2(s, b));
         gptr.assign((size_t)S.n + 1, 0);
         for (int32_t s = 0; s < ns; s++)
             for (int64_t q = S.rptr[s]; q < S.rptr[s + 1]; q++) gptr[S.rows[q] + 1]++;
-        for (int32_t i = 0; i < S.n; i++) gptr[i + 1] += gptr[i];
+        glong.clear();
+        for (int32_t i = 0; i < S.n; i++) {
+            if (gptr[i + 1] > GATHER_LONG) glong.push_back(i);
+            gptr[i + 1] += gptr[i];
+        }
         glist.resize((size_t)gptr[S.n]);
         {
             std::vector<int64_t> fill(gptr.begin(), gptr.end() - 1);
@@ -784,7 +800,7 @@ struct Layout {
     size_t pan, upd, ea, flist, dscr, dinv, dscr_off, slist, sfwd, sbelow, sbwd, sasm, part, ztasks;
     size_t sblk, sbsum, xinvt, xoff, xinv, part2, dinvt, altt, alt2, gptr, glist;
     size_t spchunk, splong, sppart, iperm, leafq, leafc, diagf, stept, spgrp, spgit, spglong;
-    size_t swt, swi, swx;
+    size_t swt, swi, swx, glong;
     // LU factors only: the U^T fronts and their diagonal-block scratch, inverses and super-block inverses
     size_t fronts_u = 0, dscr_u = 0, dinv_u = 0, xinv_u = 0;
     size_t total;
@@ -867,6 +883,7 @@ struct Layout {
         diagf = seg(std::max<size_t>(1, P.diag_fronts.size()) * 4);
         stept = seg(std::max<size_t>(1, P.step_tasks.size()) * sizeof(int4));
         swt = seg(P.sw_tasks.size() * sizeof(SweepTask));
+        glong = seg(std::max<size_t>(1, P.glong.size()) * 4);
         swi = seg(P.sw_items.size() * sizeof(SweepItem));
         // exchange arrays (z, w, v, x), then ctl
         swx = seg(P.sw_ok ? (size_t)4 * n * std::min(k, SWEEP_MAX_RHS) * esz + 16 : 0);
@@ -1593,11 +1610,22 @@ int launch_apply(wcs_factor f, int part, int k, double *B, int64_t ld, hipStream
         hipLaunchKernelGGL(k_rows_out<T>, dim3(grid_for(nk)), dim3(256), 0, st, (const T *)W, n, k, B, ld);
     } else {
         hipLaunchKernelGGL(k_rows_in<T>, dim3(grid_for(nk)), dim3(256), 0, st, B, ld, n, k, Y);
-        if (!P.al_tasks.empty())
-            hipLaunchKernelGGL(k_apply_l<T>, dim3((unsigned)P.al_tasks.size()), dim3(THREADS), 0, st,
-                               f->at<int2>(Lo.alt2), a, (const T *)Y, W);
-        hipLaunchKernelGGL(k_apply_gather<T>, dim3(grid_for(nk)), dim3(256), 0, st, f->at<int64_t>(Lo.gptr),
-                           f->at<int64_t>(Lo.glist), n, k, (const T *)W, Y);
+        // short contractions by a wave per tile (its vector accesses need k a multiple of 4)
+        const int64_t nt = (int64_t)P.al_tasks.size(), nl = k % 4 == 0 ? P.al_long : nt;
+        if (P.al_strip)
+            hipLaunchKernelGGL(k_apply_l_strip<T>, dim3((unsigned)P.al_strip, (unsigned)((k + 15) / 16)), dim3(THREADS),
+                               0, st, f->at<int2>(Lo.alt2), a, (const T *)Y, W);
+        if (nl > P.al_strip)
+            hipLaunchKernelGGL(k_apply_l<T>, dim3((unsigned)(nl - P.al_strip)), dim3(THREADS), 0, st,
+                               f->at<int2>(Lo.alt2) + P.al_strip, a, (const T *)Y, W);
+        if (nt > nl)
+            hipLaunchKernelGGL(k_apply_l1<T>, dim3((unsigned)((nt - nl + 3) / 4)), dim3(THREADS), 0, st,
+                               f->at<int2>(Lo.alt2) + nl, (int)(nt - nl), a, (const T *)Y, W);
+        int kk = 1;
+        while (kk < 64 && kk < k) kk *= 2;
+        hipLaunchKernelGGL(k_apply_gather<T>, dim3((unsigned)((n + 3) / 4 + P.glong.size())), dim3(THREADS), 0, st,
+                           f->at<int64_t>(Lo.gptr), f->at<int64_t>(Lo.glist), f->at<int32_t>(Lo.glong), n, k, kk,
+                           (const T *)W, Y);
         hipLaunchKernelGGL(k_perm_out<T>, dim3(grid_for(nk)), dim3(256), 0, st, (const T *)Y, perm, n, k, B, ld,
                            (const double *)nullptr, 0);
     }
@@ -2130,6 +2158,7 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
     rc = rc ? rc : upload(f, L.stept, P.step_tasks, st);
     rc = rc ? rc : upload(f, L.swt, P.sw_tasks, st);
     rc = rc ? rc : upload(f, L.swi, P.sw_items, st);
+    rc = rc ? rc : upload(f, L.glong, P.glong, st);
     std::vector<int32_t> segp = S.seg_ptr.size() >= 2 ? S.seg_ptr : std::vector<int32_t>{0, S.n};
     rc = rc ? rc : upload(f, L.segp, segp, st);
     if (rc == WCS_OK) {

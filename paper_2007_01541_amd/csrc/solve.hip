@@ -1506,6 +1506,8 @@ __global__ __launch_bounds__(THREADS, sizeof(T) == 4 ? 3 : 2) void k_apply_lt(co
     }
 }
 
+constexpr int APPLY_WAVE_K = 128, APPLY_STRIP_K = 1024;
+
 // L Y, first pass: task = (front, 64-row tile).  W row woff[f] + r of the
 // front's own row block gets sum over its pivot columns c <= r of
 // L(r, c) Yin(first + c); k_apply_gather then adds up, for every row of Y,
@@ -1548,19 +1550,184 @@ __global__ __launch_bounds__(THREADS, sizeof(T) == 4 ? 3 : 2) void k_apply_l(con
     }
 }
 
-// L Y, second pass: Y(i) = sum of the W rows glist[gptr[i] .. gptr[i+1]) (in
-// that fixed order: fronts ascending), i.e. every front's contribution to row i
+// The same for tiles of more than APPLY_STRIP_K pivot columns: task = (front,
+// 64-row tile), grid y = 16 columns of the right-hand sides.  The few tiles of
+// a large separator have thousands of pivot columns each and their time is
+// that of one workgroup's chain of loads: the strips give four times the
+// workgroups and 64 pivot columns of L in flight per wave.  They also read L
+// four times, so shorter tiles, of which there are many, stay with k_apply_l
+// (N = 65,536, 64 FP64 columns, tiles of more than 128 pivot columns: 435 us
+// all with k_apply_l, 650 all with strips, 440 with this split, the strips taking 195).
 template <typename T>
-__global__ void k_apply_gather(const int64_t *__restrict__ gptr, const int64_t *__restrict__ glist, int n, int k,
-                               const T *__restrict__ W, T *__restrict__ Y)
+__global__ __launch_bounds__(THREADS, 2) void k_apply_l_strip(const int2 *__restrict__ tasks, SolveArgs<T> a,
+                                                              const T *__restrict__ Yin, T *__restrict__ W)
 {
-    int64_t total = (int64_t)n * k;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        int i = (int)(idx / k), c = (int)(idx % k);
-        T s = 0;
-        for (int64_t q = gptr[i]; q < gptr[i + 1]; q++) s += W[glist[q] * k + c];
-        Y[idx] = s;
+    typedef typename Mfma<T>::V V;
+    __shared__ T red[4 * 64 * 16];
+    const int2 t = tasks[blockIdx.x];
+    const int f = t.x, r0 = t.y * SB;
+    const int m = a.mfront[f], p = a.pfront[f], k = a.k, ld = front_ld(m), first = a.first[f];
+    const int kend = min(p, r0 + SB);       // columns c <= r < r0 + SB
+    const T *L = a.fronts + a.front_off[f];
+    T *out = W + a.woff[f] * k;
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, kq = lane / 16, ln = lane % 16;
+    const int per = ((kend + 63) / 64) * 16, cb0 = wave * per, ce = min(kend, cb0 + per);
+    const int col = blockIdx.y * 16 + ln;
+    V acc[4];
+#pragma unroll
+    for (int x = 0; x < 4; x++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc[x][e] = 0;
+    for (int kg = cb0; kg < ce; kg += 64) {
+        T av[16][4], bv[16];
+        const bool edge = kg + 64 > ce || kg + 64 > r0 || r0 + 64 > m;     // columns past the end, or above the diagonal
+#pragma unroll
+        for (int s = 0; s < 16; s++) {
+            const int c = kg + 4 * s + kq;
+            bv[s] = c < ce && col < k ? Yin[(int64_t)(first + c) * k + col] : (T)0;
+#pragma unroll
+            for (int x = 0; x < 4; x++) {
+                const int r = r0 + 16 * x + ln;
+                if (!edge) av[s][x] = L[(int64_t)c * ld + r];
+                else av[s][x] = (c < ce && r < m && c <= r) ? L[(int64_t)c * ld + r] : (T)0;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 16; s++)
+#pragma unroll
+            for (int x = 0; x < 4; x++) acc[x] = Mfma<T>::mma(av[s][x], bv[s], acc[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; x++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) red[(wave * 64 + 16 * x + Mfma<T>::row(kq, e)) * 16 + ln] = acc[x][e];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int e = tid + THREADS * q, r = r0 + e / 16, c = blockIdx.y * 16 + e % 16;
+        if (r < m && c < k)
+            out[(int64_t)r * k + c] = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
+    }
+}
+
+// The same for tiles of at most APPLY_WAVE_K pivot columns and k a multiple of
+// 4: a wave per tile with the whole contraction, stored straight from the
+// accumulators.  Nearly all tiles are such; with four waves per tile each had
+// one group of loads to multiply and then a reduction through 64 KB of LDS, two
+// workgroups per compute unit (N = 65,536, 64 FP64 columns: 170 us for these tiles, about 240 before).
+template <typename T>
+__global__ __launch_bounds__(THREADS, 2) void k_apply_l1(const int2 *__restrict__ tasks, int ntasks, SolveArgs<T> a,
+                                                         const T *__restrict__ Yin, T *__restrict__ W)
+{
+    typedef typename Vec4<T>::type V4;
+    const int ti = blockIdx.x * (THREADS / 64) + threadIdx.x / 64;
+    if (ti >= ntasks) return;
+    const int2 t = tasks[ti];
+    const int f = t.x, r0 = t.y * SB;
+    const int m = a.mfront[f], p = a.pfront[f], k = a.k, ld = front_ld(m), first = a.first[f];
+    const T *L = a.fronts + a.front_off[f];
+    T *out = W + a.woff[f] * k;
+    const int lane = threadIdx.x % 64, kq = lane / 16, ln = lane % 16;
+    for (int c0 = 0; c0 < k; c0 += 64) {
+        typename Mfma<T>::V acc[4][4];
+#pragma unroll
+        for (int x = 0; x < 4; x++)
+#pragma unroll
+            for (int y = 0; y < 4; y++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[x][y][e] = 0;
+        wave_mm_q<T>(
+            acc, 0, min(p, r0 + SB),
+            [&](int q, int c) {
+                // four rows of L; above the diagonal (where the front holds other data) zero
+                const int r = r0 + 4 * q;
+                V4 v = r < m ? *reinterpret_cast<const V4 *>(L + (int64_t)c * ld + r) : V4{0, 0, 0, 0};
+                if (r < c) v.x = 0;
+                if (r + 1 < c) v.y = 0;
+                if (r + 2 < c) v.z = 0;
+                if (r + 3 < c) v.w = 0;
+                return v;
+            },
+            [&](int c, int q) {
+                const int col = c0 + 4 * q;
+                return col < k ? *reinterpret_cast<const V4 *>(Yin + (int64_t)(first + c) * k + col) : V4{0, 0, 0, 0};
+            });
+        const int col = c0 + 4 * ln;
+#pragma unroll
+        for (int x = 0; x < 4; x++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int r = r0 + 4 * Mfma<T>::row(kq, e) + x;
+                V4 v;
+                v.x = acc[x][0][e];
+                v.y = acc[x][1][e];
+                v.z = acc[x][2][e];
+                v.w = acc[x][3][e];
+                if (r < m && col < k) *reinterpret_cast<V4 *>(out + (int64_t)r * k + col) = v;
+            }
+    }
+}
+
+// L Y, second pass: Y(i) = sum of the W rows glist[gptr[i] .. gptr[i+1]), i.e.
+// every front's contribution to row i, in a fixed order.  The first (n + 3) / 4
+// workgroups take four rows each, one per wave; a row held by more than
+// GATHER_LONG fronts (a separator near the root is in every front below it) has
+// a workgroup of its own afterwards.  A wave reads 64 / kk list entries at a
+// time, kk lanes each (kk: min(k, 64) rounded up to a power of two), GATHER_U of
+// them in flight.  (One thread per element walking its list alone took as long
+// as the longest list: 742 us at N = 65,536 with 64 FP64 columns; this form 195.)
+constexpr int GATHER_LONG = 64, GATHER_U = 16;
+template <typename T>
+__global__ __launch_bounds__(THREADS) void k_apply_gather(const int64_t *__restrict__ gptr,
+                                                          const int64_t *__restrict__ glist,
+                                                          const int32_t *__restrict__ glong, int n, int k, int kk,
+                                                          const T *__restrict__ W, T *__restrict__ Y)
+{
+    __shared__ T part[4][64];
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, sub = lane / kk, c = lane % kk, ns = 64 / kk;
+    // sum of entries q0 + sub, q0 + sub + ns, ... < q1 of one column chunk, complete in lanes < kk
+    auto sum = [&](int64_t q0, int64_t q1, int c0) {
+        T s[GATHER_U];
+#pragma unroll
+        for (int u = 0; u < GATHER_U; u++) s[u] = 0;
+        for (int64_t q = q0 + sub; q - sub < q1; q += GATHER_U * ns) {
+            // no branch around a load: past the end the last entry again, not added
+            int64_t row[GATHER_U];
+            T w[GATHER_U];
+#pragma unroll
+            for (int u = 0; u < GATHER_U; u++) row[u] = glist[q + u * ns < q1 ? q + u * ns : q1 - 1];
+#pragma unroll
+            for (int u = 0; u < GATHER_U; u++) w[u] = W[row[u] * k + min(c0 + c, k - 1)];
+#pragma unroll
+            for (int u = 0; u < GATHER_U; u++)
+                if (q + u * ns < q1) s[u] += w[u];
+        }
+        T v = 0;
+#pragma unroll
+        for (int u = 0; u < GATHER_U; u++) v += s[u];
+        for (int h = kk; h < 64; h *= 2) v += __shfl_xor(v, h, 64);
+        return v;
+    };
+    const int nshort = (n + 3) / 4;
+    if ((int)blockIdx.x < nshort) {
+        const int i = blockIdx.x * 4 + wave;
+        if (i >= n) return;
+        const int64_t g0 = gptr[i], g1 = gptr[i + 1];
+        if (g1 - g0 > GATHER_LONG) return;
+        for (int c0 = 0; c0 < k; c0 += 64) {
+            const T v = sum(g0, g1, c0);
+            if (lane < kk && c0 + c < k) Y[(int64_t)i * k + c0 + c] = v;
+        }
+        return;
+    }
+    const int i = glong[blockIdx.x - nshort];
+    const int64_t g0 = gptr[i], g1 = gptr[i + 1], per = (g1 - g0 + 3) / 4, q0 = g0 + wave * per;
+    for (int c0 = 0; c0 < k; c0 += 64) {
+        if (c0) __syncthreads();
+        part[wave][lane] = sum(q0, q0 + per < g1 ? q0 + per : g1, c0);
+        __syncthreads();
+        if (threadIdx.x < kk && c0 + c < k)
+            Y[(int64_t)i * k + c0 + c] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
     }
 }
 
