@@ -1005,23 +1005,25 @@ __global__ __launch_bounds__(THREADS) void k_diag_inv(const int2 *__restrict__ t
 // The front's pivot columns (m x p, zeroed and filled with A beforehand) are
 // staged in LDS, column-major with leading dimension sld (= 16 mod 32, so the
 // four k-columns a wave reads per matrix-core step fall in distinct bank
-// halves), and factored by right-looking column steps (l_jj = sqrt(a_jj),
-// l_ij = a_ij / l_jj below it, then the later pivot columns updated by the
-// rank-one product; each element by one thread in a fixed order).  The
-// factored panel goes back to the front and its diagonal block to the
-// diagonal-block scratch (as the panel kernel's block, identity-padded);
-// then the update matrix C = -L21 L21^T (lower triangle; a leaf has no
-// children, so it is assigned) is formed on the matrix cores straight from
-// the LDS copy, 64 x 64 tiles spread over the waves.  Fronts that fit:
-// p <= NB and sld * p <= LeafCfg<T>::ELEMS (the plan routes the others to the
-// level-synchronous kernels, which run beside this launch).  A non-positive pivot is reported as in the
-// panel kernel.
-// LDS of the staged panel: FP32 80 KB (two workgroups per compute unit),
-// FP64 156 KB (one); either holds the pivot columns of nearly every leaf
-// front of the benchmark matrices
+// halves).  The diagonal block is factored by factor_diag_block; then the
+// waves take 64 rows below it at a time and solve them by 16-column blocks as
+// the panel kernel does, operands and result in LDS.  (Column steps over the
+// whole panel, three barriers each, were bound by their own chain: N = 1,024
+// FP64 184 -> 69 us, N = 4,096 FP32 108 -> 46, N = 262,144
+// 1309 and 764 us before.)  The factored
+// panel goes back to the front and its diagonal block to the diagonal-block
+// scratch (identity-padded); then the update matrix C = -L21 L21^T (lower
+// triangle; a leaf has no children, so it is assigned) is formed on the matrix
+// cores straight from the LDS copy, 64 x 64 tiles spread over the waves.
+// Fronts that fit: p <= NB and sld * p <= LeafCfg<T>::ELEMS (the plan routes
+// the others to the level-synchronous kernels, which run beside this launch).
+// A non-positive pivot is reported as in the panel kernel.
+// LDS: FP32 80 KB (two workgroups per compute unit), FP64 156 KB (one), less
+// the diagonal block and its sub-block inverses
 template <typename T> struct LeafCfg {
+    static constexpr int DIAG = NB * (NB + 1) + NB / 16 * 16 * 17 + NB;     // elements
     static constexpr int BYTES = sizeof(T) == 4 ? 81920 - 64 : 159744 - 64;
-    static constexpr int ELEMS = BYTES / (int)sizeof(T);
+    static constexpr int ELEMS = BYTES / (int)sizeof(T) - DIAG;
     static constexpr int PER_CU = sizeof(T) == 4 ? 2 : 1;
 };
 __host__ __device__ inline int leaf_sld(int m) { return ((m + 15) / 32) * 32 + 16; }
@@ -1037,45 +1039,90 @@ __global__ __launch_bounds__(THREADS, LeafCfg<T>::PER_CU) void k_leaf(const int3
                                                      T *__restrict__ dscr, int32_t *__restrict__ bad)
 {
     __shared__ __align__(16) T S[LeafCfg<T>::ELEMS];
+    __shared__ T A[NB][NB + 1];     // the diagonal block, column-major; becomes L
+    __shared__ DiagInv<T> Iv;       // inverses of its 16 x 16 diagonal sub-blocks
+    __shared__ T Rd[NB];
     __shared__ int s_task;
     typedef typename Mfma<T>::V V;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int kq = lane / 16, ln = lane % 16;
+    // workgroup barrier after this wave's LDS accesses (the explicit wait: see Sweep::sync)
+    auto sync = [] {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
     for (;;) {
         if (tid == 0) s_task = atomicAdd(counter, 1);
-        __syncthreads();
+        sync();
         const int q = s_task;
-        __syncthreads();                  // every thread has read s_task (and the last front's LDS use is over)
+        sync();                           // every thread has read s_task (and the last front's LDS use is over)
         if (q >= nq) break;
         const int f = queue[q];
         const int m = mfront[f], p = pfront[f], ld = front_ld(m), sld = leaf_sld(m);
         T *F = fronts + front_off[f];
-        for (int c = 0; c < p; c++)
-            for (int r = c + tid; r < m; r += THREADS) S[c * sld + r] = F[(int64_t)c * ld + r];
-        for (int j = 0; j < p; j++) {
-            __syncthreads();              // column j is final
-            T d = S[j * sld + j];
-            if (!(d > (T)0)) {
-                if (tid == 0) atomicMin(bad, first[f] + j);
-                d = (T)1;
+        // a wave per column, eight columns' loads in flight
+        for (int c0 = wave; c0 < p; c0 += 32)
+            for (int r = lane; r < m; r += 64) {
+                T v[8];
+#pragma unroll
+                for (int u = 0; u < 8; u++) v[u] = F[(int64_t)min(c0 + 4 * u, p - 1) * ld + r];
+#pragma unroll
+                for (int u = 0; u < 8; u++) {
+                    const int c = c0 + 4 * u;
+                    if (c >= p) continue;
+                    if (r >= c) S[c * sld + r] = v[u];
+                    if (r < NB) A[c][r] = r < p && r >= c ? v[u] : (T)0;
+                }
             }
-            const T rp = rsqrt_refined(d);
-            __syncthreads();              // every thread has read the pivot
-            for (int i = j + tid; i < m; i += THREADS) S[j * sld + i] = i == j ? d * rp : S[j * sld + i] * rp;
-            __syncthreads();
-            for (int c = j + 1; c < p; c++) {
-                const T lc = S[j * sld + c];
-                for (int i = c + tid; i < m; i += THREADS) S[c * sld + i] -= S[j * sld + i] * lc;
-            }
-        }
-        __syncthreads();
-        for (int c = 0; c < p; c++)
-            for (int r = c + tid; r < m; r += THREADS) F[(int64_t)c * ld + r] = S[c * sld + r];
-        T *D = dscr + dscr_off[f];
+        // the padding of the diagonal block: rows past m, columns past p
         for (int e = tid; e < NB * NB; e += THREADS) {
-            int c = e / NB, r = e % NB;
-            D[e] = (r < p && c < p && r >= c) ? S[c * sld + r] : (r == c ? (T)1 : (T)0);
+            const int c = e / NB, r = e % NB;
+            if (c >= p || r >= m) A[c][r] = r == c ? (T)1 : (T)0;
         }
+        sync();
+        factor_diag_block<T>(A, Iv, Rd, p, true, bad, first[f], [](auto) {});
+        // rows below, 64 per wave and turn: xs[c][rb] is the transposed 16 x 16
+        // block (rows row0 + 16 rb.., columns 16 c..), as in k_panel
+        for (int row0 = p + 64 * wave; row0 < m; row0 += THREADS) {
+            V xs[NB / 16][4];
+#pragma unroll
+            for (int c = 0; c < NB / 16; c++)
+#pragma unroll
+                for (int rb = 0; rb < 4; rb++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const int row = row0 + rb * 16 + ln, k = c * 16 + Mfma<T>::row(kq, e);
+                        xs[c][rb][e] = (row < m && k < p) ? S[k * sld + row] : (T)0;
+                    }
+            static_for<0, NB / 16, 1>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                if (16 * c >= p) return;
+#pragma unroll
+                for (int rb = 0; rb < 4; rb++) {
+                    V acc = xs[c][rb];
+#pragma unroll
+                    for (int j = 0; j < c; j++)
+#pragma unroll
+                        for (int st = 0; st < 4; st++)
+                            acc = Mfma<T>::mma(-A[16 * j + Mfma<T>::row(kq, st)][16 * c + ln], xs[j][rb][st], acc);
+                    V x = {0, 0, 0, 0};
+#pragma unroll
+                    for (int st = 0; st < 4; st++) x = Mfma<T>::mma(Iv[c][Mfma<T>::row(kq, st)][ln], acc[st], x);
+                    xs[c][rb] = x;
+                    const int row = row0 + rb * 16 + ln;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const int k = 16 * c + Mfma<T>::row(kq, e);
+                        if (row < m && k < p) S[k * sld + row] = x[e];
+                    }
+                }
+            });
+        }
+        sync();
+        T *D = dscr + dscr_off[f];
+        for (int e = tid; e < NB * NB; e += THREADS) D[e] = A[e / NB][e % NB];
+        for (int c = wave; c < p; c += 4)
+            for (int r = c + lane; r < m; r += 64) F[(int64_t)c * ld + r] = r < p ? A[c][r] : S[c * sld + r];
         // update matrix, 64 x 64 tiles of the lower triangle from row and column
         // p rounded down to 4 (earlier rows and columns masked), round robin
         // over the waves.  The A operand takes the tile rows in the order that

@@ -1,0 +1,54 @@
+"""The leaf kernel at the edges of its tiles: dense blocks of p pivots under a
+common dense border of s rows (whole and partial 16-column blocks, 64-row
+slabs, one row, no rows), against a double-precision factorization on the host
+within the backward-error bound of Cholesky.
+"""
+import numpy as np
+import pytest
+
+from tests.helpers import EPS32, EPS64
+from tests.test_gpu_parity import dev
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+from paper_2007_01541_amd import FP32, FP64, Factor, Symbolic  # noqa: E402
+
+
+def bordered(p, s, blocks, seed):
+    """Dense SPD matrix, zero between the blocks; the lower triangle by columns."""
+    n = p * blocks + s
+    rng = np.random.default_rng(seed)
+    G = rng.uniform(-1.0, 1.0, (n, n))
+    G = (G + G.T) / 2
+    for b in range(blocks):
+        lo, hi = b * p, (b + 1) * p
+        G[lo:hi, :lo] = 0
+        G[lo:hi, hi:blocks * p] = 0
+    G[np.diag_indices(n)] = n
+    keep = np.tril(G != 0)
+    colptr = np.concatenate([[0], np.cumsum(keep.sum(0))]).astype(np.int64)
+    rowind = np.concatenate([np.flatnonzero(keep[:, c]) for c in range(n)]).astype(np.int32)
+    return G, colptr, rowind, np.concatenate([G[keep[:, c], c] for c in range(n)])
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("p,s", [(1, 0), (1, 3), (15, 1), (16, 48), (17, 63), (63, 65), (64, 0), (64, 130)])
+def test_leaf_tiles(p, s, prec):
+    G, colptr, rowind, values = bordered(p, s, 3 if s else 1, 11 * p + s)
+    n = G.shape[0]
+    sym = Symbolic(n, colptr, rowind, leaf_size=64, dense_degree_min=p + s if s else 4096)
+    ex = sym.export()
+    print(f"p={p} s={s} prec={prec} fronts {np.diff(ex['relaxed_ptr'])}", flush=True)
+    f = Factor(sym, prec, max_nrhs=1)
+    f.numeric(dev(values))
+    Lp, Li, Lx = f.export_L()
+    L = np.zeros((n, n))
+    for c in range(n):
+        L[Li[Lp[c]:Lp[c + 1]], c] = Lx[Lp[c]:Lp[c + 1]]
+    P = G[np.ix_(ex["perm"], ex["perm"])]
+    if prec == FP32:
+        P = P.astype(np.float32).astype(np.float64)     # the values as the FP32 factorization reads them
+    # |A - L L^T| <= gamma |L| |L^T|; a multiple of n + 1 for the blocks' inverses
+    gamma = 4 * (n + 1) * (EPS64 if prec == FP64 else EPS32)
+    assert np.all(np.abs(P - L @ L.T) <= gamma * (np.abs(L) @ np.abs(L).T))
