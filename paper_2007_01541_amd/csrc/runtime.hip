@@ -52,6 +52,9 @@ int expand_side_blocks()
     return b > 0 ? b : 256;
 }
 
+// the value expansion's source indices fit 32 bits (they are in [0, stored entries))
+bool narrow_src(const Symbolic &S) { return S.csr_src.size() <= (size_t)INT32_MAX; }
+
 size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // independent diagonal blocks of the matrix (1 unless it is a batch)
@@ -238,6 +241,7 @@ struct Plan {
     int32_t nbo = 512;                            // outer block of this plan
     // persistent sweeps for few right-hand sides (k_sweep): forward tasks, then backward ones
     std::vector<SweepTask> sw_tasks;
+    std::vector<int32_t> src32;                // Symbolic::csr_src where it fits, until it is uploaded
     std::vector<SweepItem> sw_items;
     int64_t sw_fwd = 0;
     bool sw_ok = false;
@@ -841,7 +845,7 @@ struct Layout {
         perm = seg(n * 4);
         csr_ptr = seg((n + 1) * 8);
         csr_col = seg(S.csr_col.size() * 4);
-        csr_src = seg(S.csr_src.size() * 8);
+        csr_src = seg(S.csr_src.size() * (narrow_src(S) ? 4 : 8));
         csr_val = seg(S.csr_col.size() * 8);
         rowind = seg((size_t)S.nnz * 4);
         colof = seg((size_t)S.nnz * 4);
@@ -898,6 +902,13 @@ bool valid_prec(wcs_precision p) { return p == WCS_FP64 || p == WCS_FP32 || p ==
 // Update kernel used before any autotuning: on large fronts the streamed form
 // is the faster one in FP64 and the register-staged one in FP32.
 int32_t default_update_variant(wcs_precision p) { return p == WCS_FP32 ? WCS_UPD_REG128 : WCS_UPD_STREAM128; }
+
+// grid of a pass by XCD_CHUNK entries: a multiple of XCDS, about `most` at most
+dim3 xcd_grid(int64_t entries, int most)
+{
+    const int64_t g = std::clamp<int64_t>((entries + XCD_CHUNK - 1) / XCD_CHUNK, 1, most);
+    return dim3((unsigned)((g + XCDS - 1) / XCDS * XCDS));
+}
 
 int grid_for(int64_t work, int threads = 256)
 {
@@ -1141,7 +1152,7 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
                                f->at<int32_t>(Lo.iperm), S.nnz, fronts, fronts_u);
     }
     if (!lu)
-        hipLaunchKernelGGL(k_scatter<T>, dim3(grid_for(S.nnz)), dim3(256), 0, st, values, f->at<int64_t>(Lo.amap),
+        hipLaunchKernelGGL(k_scatter<T>, xcd_grid(S.nnz, 1 << 16), dim3(256), 0, st, values, f->at<int64_t>(Lo.amap),
                            S.nnz, fronts);
     PROF_END(KC_SCATTER);
     if (prof) {
@@ -1640,10 +1651,13 @@ int ensure_csr_values(wcs_factor f, const double *values, hipStream_t st, bool b
 {
     const Symbolic &S = *f->S;
     int64_t nz = (int64_t)S.csr_col.size();
-    int grid = grid_for(nz);
-    if (beside) grid = std::min(grid, expand_side_blocks());
-    hipLaunchKernelGGL(k_expand_values, dim3(grid), dim3(256), 0, st, values,
-                       f->at<int64_t>(f->lay.csr_src), nz, f->at<double>(f->lay.csr_val));
+    const dim3 g = xcd_grid(nz, beside ? expand_side_blocks() : 1 << 16);
+    if (narrow_src(S))
+        hipLaunchKernelGGL(k_expand_values<int32_t>, g, dim3(256), 0, st, values, f->at<int32_t>(f->lay.csr_src), nz,
+                           f->at<double>(f->lay.csr_val));
+    else
+        hipLaunchKernelGGL(k_expand_values<int64_t>, g, dim3(256), 0, st, values, f->at<int64_t>(f->lay.csr_src), nz,
+                           f->at<double>(f->lay.csr_val));
     HIP_TRY(hipGetLastError());
     return WCS_OK;
 }
@@ -1982,6 +1996,7 @@ int new_factor(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, wcs_facto
         f->prec = prec;
         f->max_nrhs = max_nrhs;
         f->plan.build(*f->S, elem_size(prec), prec != WCS_LU64 && leaf_kernel_enabled(), prec != WCS_LU64);
+        if (narrow_src(*f->S)) f->plan.src32.assign(f->S->csr_src.begin(), f->S->csr_src.end());
         for (Level &L : f->plan.levels) L.upd_var = default_update_variant(prec);
         f->lay.compute(*f->S, f->plan, elem_size(prec), max_nrhs, is_lu(prec));
     } catch (const std::bad_alloc &) {
@@ -2114,7 +2129,10 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
     rc = rc ? rc : upload(f, L.perm, S.perm, st);
     rc = rc ? rc : upload(f, L.csr_ptr, S.csr_ptr, st);
     rc = rc ? rc : upload(f, L.csr_col, S.csr_col, st);
-    rc = rc ? rc : upload(f, L.csr_src, S.csr_src, st);
+    if (narrow_src(S))
+        rc = rc ? rc : upload(f, L.csr_src, P.src32, st);
+    else
+        rc = rc ? rc : upload(f, L.csr_src, S.csr_src, st);
     rc = rc ? rc : upload(f, L.spchunk, f->plan.spmv_chunks, st);
     rc = rc ? rc : upload(f, L.splong, f->plan.spmv_long, st);
     rc = rc ? rc : upload(f, L.spgrp, f->plan.spmv_grp, st);
@@ -2169,6 +2187,7 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
         }
     }
     if (rc) { delete f; return rc; }
+    std::vector<int32_t>().swap(f->plan.src32);
     *out = f;
     return WCS_OK;
 }
