@@ -169,64 +169,6 @@ __global__ __launch_bounds__(256) void k_extend_add(const int2 *__restrict__ tas
 }
 
 // ---------------------------------------------------------------- panel
-// Broadcast of lane v (a compile-time constant after unrolling) of each row of
-// 16 lanes to its row: a DPP row_newbcast move, which stays in the vector
-// unit (no round trip through a scalar register, as v_readlane takes).
-template <int V>
-__device__ __forceinline__ int row_bcast_i(int x)
-{
-    return __builtin_amdgcn_mov_dpp(x, 0x150 + V, 0xF, 0xF, true);
-}
-template <int V>
-__device__ __forceinline__ float row_bcast_t(float x)
-{
-    return __int_as_float(row_bcast_i<V>(__float_as_int(x)));
-}
-template <int V>
-__device__ __forceinline__ double row_bcast_t(double x)
-{
-    return __hiloint2double(row_bcast_i<V>(__double2hiint(x)), row_bcast_i<V>(__double2loint(x)));
-}
-template <typename T>
-__device__ __forceinline__ T row_bcast(T x, int v)
-{
-    switch (v) {
-    case 0: return row_bcast_t<0>(x);
-    case 1: return row_bcast_t<1>(x);
-    case 2: return row_bcast_t<2>(x);
-    case 3: return row_bcast_t<3>(x);
-    case 4: return row_bcast_t<4>(x);
-    case 5: return row_bcast_t<5>(x);
-    case 6: return row_bcast_t<6>(x);
-    case 7: return row_bcast_t<7>(x);
-    case 8: return row_bcast_t<8>(x);
-    case 9: return row_bcast_t<9>(x);
-    case 10: return row_bcast_t<10>(x);
-    case 11: return row_bcast_t<11>(x);
-    case 12: return row_bcast_t<12>(x);
-    case 13: return row_bcast_t<13>(x);
-    case 14: return row_bcast_t<14>(x);
-    default: return row_bcast_t<15>(x);
-    }
-}
-
-// 1 / sqrt(d) to working precision: the hardware estimate refined by Newton
-// steps r <- r (3 - d r^2) / 2 (two for FP64, one for FP32), so that a pivot
-// costs one square-root estimate and multiplications instead of a correctly
-// rounded square root and divisions.
-__device__ __forceinline__ double rsqrt_refined(double d)
-{
-    double r = __builtin_amdgcn_rsq(d);
-    r = r * (1.5 - 0.5 * d * r * r);
-    r = r * (1.5 - 0.5 * d * r * r);
-    return r;
-}
-__device__ __forceinline__ float rsqrt_refined(float d)
-{
-    float r = __builtin_amdgcn_rsqf(d);
-    return r * (1.5f - 0.5f * d * r * r);
-}
-
 // 16 x 16 x 16 product on one wave: acc += X * Y with X(r, k) = fx(r, k),
 // Y(k, n) = fy(k, n); the caller maps acc element e of lane l to
 // C(Mfma<TD>::row(l/16, e), l%16).
