@@ -651,7 +651,7 @@ def main() -> int:
     top = levels[-3:]
     root_ms = sum(l["ms"] for l in top)
     root_flops = sum(l["flops"] for l in top)
-    root = {"levels": len(top), "schedule": "height in the assembly tree; fronts of >= 1024 pivots one level below "
+    root = {"levels": len(top), "schedule": "height in the assembly tree; fronts of >= 256 pivots one level below "
                                             "their parent", "ms": root_ms, "tflops": root_flops / root_ms / 1e9,
             "pct_fp32_mfma_peak": 100 * root_flops / root_ms / 1e9 / PEAK["fp32_mfma_tflops"],
             "per_level": [{"ms": round(l["ms"], 3), "tflops": round(l["flops"] / max(l["ms"], 1e-9) / 1e9, 2)}
