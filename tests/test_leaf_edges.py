@@ -52,3 +52,22 @@ def test_leaf_tiles(p, s, prec):
     # |A - L L^T| <= gamma |L| |L^T|; a multiple of n + 1 for the blocks' inverses
     gamma = 4 * (n + 1) * (EPS64 if prec == FP64 else EPS32)
     assert np.all(np.abs(P - L @ L.T) <= gamma * (np.abs(L) @ np.abs(L).T))
+
+
+def test_leaf_pivots_to_the_last_place():
+    """FP64 leaf pivots sqrt(d) over the mantissas of two binades (diagonal
+    matrix: every front is a leaf).  The second Newton step r' = r (3/2 - d r^2 / 2)
+    rounds d r^2 / 2 (about 1/2) three times and its difference and product once
+    each, l = d r' once more: less than 4 units u = eps / 2 in all, against up to
+    1.5 2^-48 = 24 eps from one step on an estimate of 24 bits."""
+    n = 4096
+    d = np.random.default_rng(5).uniform(1.0, 4.0, n)
+    f = Factor(Symbolic(n, np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32)), FP64, max_nrhs=1)
+    f.numeric(dev(d))
+    Lp, Li, Lx = f.export_L()
+    L = np.zeros(n)
+    L[f.sym.export()["perm"]] = Lx[Lp[:-1]]
+    ref = np.sqrt(d.astype(np.longdouble))
+    worst = float((np.abs(L - ref) / ref).max() / EPS64)
+    print(f"largest error {worst:.2f} eps", flush=True)
+    assert worst <= 2.0
