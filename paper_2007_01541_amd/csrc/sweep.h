@@ -32,7 +32,9 @@
 //
 // Arithmetic: forward, a row subtracts one sum per 256-pivot super-block;
 // backward, a column subtracts one sum per 256 rows; each is formed from the
-// waves' partial sums.  All orders are fixed, so results are deterministic.
+// waves' partial sums, the forward solves' diagonal term last.  All orders are
+// fixed, so results are deterministic; they depend on the number of right-hand
+// sides through the kernel's width (1, 4 or 8 columns) alone.
 #pragma once
 #include "common.h"
 
@@ -424,6 +426,17 @@ template <typename T, int KT> struct Sweep {
         own(nr, [&](int q, int r, int c) { st_dev(a.W + (D.woff + r0 + r) * k + c, out(v[q])); });
     }
 
+    // The forward solves' rows of X = L_SS^-1 end with their largest element, the
+    // diagonal one.  Summed with the others, in whatever order, it is rounded
+    // at every later addition; so the lanes take a zero instead (from above the
+    // diagonal, where the inverse of a 64-block is zero) and the thread that
+    // owns the row adds X_rr w_r last.  (Relative error of FP32 L^-1 b at N =
+    // 16,384, 1, 4 and 7 right-hand sides: 8.16, 7.85 and 7.48e-8 without,
+    // 6.84, 6.89 and 6.90e-8 so; the level-by-level kernels 7.04, 7.07 and
+    // 7.87e-8.  Full solves take 0-1% longer at 1-4, 0-2% less at 8.)  Offset
+    // in X of that zero for row r:
+    __device__ __forceinline__ static int above(int r) { return r % 64 ? -1 : 256; }
+
     // 32 pivots: w minus one product per earlier super-block, then z = X w over
     // their own super-block.  Lane l takes row l % 32 and the columns of parity
     // l / 32; element (tid / KT, tid % KT) is this thread's.
@@ -434,8 +447,10 @@ template <typename T, int KT> struct Sweep {
         const bool mine = er < nr && ec < k;
         const T *L = a.fronts + D.foff + r0 + min(lane % 32, nr - 1);
         // the super-block's rows of X, up to its own columns (zero above its diagonal blocks)
-        const T *X = a.xinv + D.xoff + (int64_t)nS * 256 * 256 + (int64_t)(min(wave, ib / 2) * 64 + half) * 256 + ib * 32 +
-                     lane % 32;
+        const int xr = ib * 32 + lane % 32, xc = min(wave, ib / 2) * 64 + half;
+        const T *XS = a.xinv + D.xoff + (int64_t)nS * 256 * 256;
+        const int ed = ib * 32 + min(er, 31);
+        const T xd = XS[(int64_t)ed * 256 + ed];
         T lv[32], xv[32], acc[KT];
         auto load = [&](int S) {
             const T *c = L + (int64_t)(S * 256 + wave * 64 + half) * ld;
@@ -448,7 +463,10 @@ template <typename T, int KT> struct Sweep {
         add_items(D);
         T v = tid < 32 * KT ? sh.w[tid] : (T)0;
 #pragma unroll
-        for (int j = 0; j < 32; j++) xv[j] = X[(int64_t)(2 * j) * 256];
+        for (int j = 0; j < 32; j++) {
+            const int c = xc + 2 * j;
+            xv[j] = XS[c * 256 + xr + (c == xr ? above(xr) : 0)];
+        }
         for (int S = 0; S < nS; S++) {
             stage(256, xz + (int64_t)(D.first + S * 256) * k);
             sync();
@@ -463,7 +481,7 @@ template <typename T, int KT> struct Sweep {
         if (tid < 32 * KT) sh.z[ib * 32 * KT + tid] = mine ? v : (T)0;
         sync();
         dot<2>(xv, wave * 64 + half, acc);
-        v = reduce32(acc);
+        v = reduce32(acc) + xd * v;
         if (mine) put_z((int64_t)(D.first + r0 + er) * k + ec, v);
     }
 
@@ -471,13 +489,23 @@ template <typename T, int KT> struct Sweep {
     __device__ void fwd_front(const SweepTask &D)
     {
         const int ld = front_ld(D.m), r = D.p + wave * 64 + lane;
-        T xv[16], lv[64];
-        const T *X = a.xinv + D.xoff + (int64_t)(wave * 16) * 256, *L = a.fronts + D.foff;
+        T xv[16], lv[64], xd[NE];
+        const T *X = a.xinv + D.xoff, *L = a.fronts + D.foff;
         const int lr = min(r, D.m - 1);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));     // or the offsets are computed once for all tasks, and spilled
 #pragma unroll
-        for (int j = 0; j < 16; j++) xv[j] = (X + j * 256)[lane];
+        for (int j = 0; j < 16; j++) {
+            const int c = wave * 16 + j;
+            xv[j] = X[c * 256 + ln + (c == ln ? above(ln) : 0)];
+        }
 #pragma unroll
         for (int j = 0; j < 64; j++) lv[j] = (L + (int64_t)min(j, D.p - 1) * ld)[lr];
+#pragma unroll
+        for (int q = 0; q < NE; q++) {
+            const int e = min((tid + THREADS * q) / KT, 63);
+            xd[q] = X[e * 256 + e];
+        }
         for (int e = tid; e < MAXR * KT; e += THREADS) {
             int rr = e / KT, c = e % KT;
             sh.w[e] = (rr < D.p && c < k) ? ld_dev(a.Y + (int64_t)(D.first + rr) * k + c) : (T)0;
@@ -489,6 +517,11 @@ template <typename T, int KT> struct Sweep {
         sync();
         dot<1>(xv, wave * 16, acc);
         reduce(acc, s);
+#pragma unroll
+        for (int q = 0; q < NE; q++) {
+            const int e = tid + THREADS * q;
+            if (e < NEL) s[q] += xd[q] * sh.w[e];
+        }
         own(D.p, [&](int q, int rr, int c) { put_z((int64_t)(D.first + rr) * k + c, s[q]); });
 #pragma unroll
         for (int q = 0; q < NE; q++) {

@@ -65,3 +65,38 @@ def test_sweeps_pass_nan_on(bits):
     B[:, 1] = np.full(m["n"], bits, np.uint64).view(np.float64)
     X = f.solve(dev(B)).cpu().numpy()
     assert np.isfinite(X[:, 0]).all() and np.isnan(X[:, 1]).all()
+
+
+@pytest.mark.parametrize("n", [64, 200, 300])
+def test_forward_sweep_rounds_the_diagonal_term_once(n):
+    """FP32 L^-1 P B with dense fronts of n pivots (a narrow one, one ragged
+    super-block, two) whose off-diagonal entries are about 1e-6 of the diagonal:
+    with u = eps / 2, z_r = X_rr w_r (1 + d) with |d| <= u for X_rr, u for the
+    product and sum and u for w_r - (rows past the first super-block); the
+    n 1e-6 of the other terms adds less than 0.1 u, their roundings at most
+    n 1e-6 (n + 10) u < 0.1 u.  B is exact in FP32; the reference uses the exported L."""
+    rng = np.random.default_rng(n)
+    G = rng.uniform(-1e-6, 1e-6, (n, n))
+    G[np.diag_indices(n)] = rng.uniform(1.0, 2.0, n)
+    colptr = np.concatenate([[0], np.cumsum(n - np.arange(n))]).astype(np.int64)
+    rowind = np.concatenate([np.arange(c, n) for c in range(n)]).astype(np.int32)
+    sym = Symbolic(n, colptr, rowind, leaf_size=n, dense_degree_min=4 * n)
+    f = Factor(sym, FP32, max_nrhs=8)
+    f.numeric(dev(np.concatenate([G[c:, c] for c in range(n)])))
+    ex = sym.export()
+    assert ex["relaxed_ptr"].size == 2, "one front"
+    Lp, Li, Lx = f.export_L()
+    L = np.zeros((n, n), np.longdouble)
+    for c in range(n):
+        L[Li[Lp[c]:Lp[c + 1]], c] = Lx[Lp[c]:Lp[c + 1]]
+    B = (rng.uniform(1.0, 2.0, (n, 8)) * rng.choice([-1.0, 1.0], (n, 8))).astype(np.float32).astype(np.float64)
+    Z = np.zeros((n, 8), np.longdouble)
+    for r in range(n):
+        Z[r] = (B[ex["perm"][r]] - L[r, :r] @ Z[:r]) / L[r, r]
+    u = EPS32 / 2
+    bound = np.where(np.arange(n) < 256, 2.2, 3.2)[:, None] * u * np.abs(Z)
+    for k in (1, 4, 8):
+        X = f.solve(dev(B[:, :k]), SOLVE_L).cpu().numpy()
+        err = np.abs(X - Z[:, :k])
+        print(f"n={n} k={k} largest error {float((err / np.abs(Z[:, :k])).max() / u):.2f} u", flush=True)
+        assert np.all(err <= bound[:, :k]), k
