@@ -52,7 +52,7 @@ typedef enum {
     WCS_OK = 0,
     WCS_EINVAL = -1,    /* malformed argument or pattern */
     WCS_ENOMEM = -2,    /* workspace too small, or host allocation failed */
-    WCS_EHIP = -3,      /* a HIP runtime call failed */
+    WCS_EHIP = -3,      /* a HIP runtime call failed, or a kernel gave up a wait (wcs_factor_check) */
     WCS_ENOTSPD = -4,   /* a pivot was not positive (or NaN): matrix not SPD */
     WCS_ENOTCONV = -5,  /* iterative refinement did not reach the tolerance */
     WCS_ESTATE = -6,    /* call not valid in the handle's current state */
@@ -252,7 +252,13 @@ int wcs_factor_export_upper(wcs_factor f, int32_t j0, int32_t j1, int64_t *Up, i
 #define WCS_STATIC_WORKSPACE_BYTES (64u << 20)
 int wcs_factor_create_static(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, wcs_stream stream,
                              wcs_factor *out);
-/* Waits for the stream; *bad_col = first failing pivot or -1; returns WCS_ENOTSPD if one failed. */
+/*
+ * Waits for the stream; *bad_col = first failing pivot or -1; returns
+ * WCS_ENOTSPD if one failed.  Solves of at most eight right-hand sides run as
+ * one kernel whose workgroups wait for one another, each wait bounded (about
+ * two seconds); a solve that gave up leaves NaN and is reported here, once, as
+ * WCS_EHIP, or by the refinement it belongs to.
+ */
 int wcs_factor_check(wcs_factor f, wcs_stream stream, int32_t *bad_col);
 void wcs_factor_free(wcs_factor f);
 /*

@@ -78,6 +78,14 @@ int32_t solve_step_min_rows()
     return e ? std::atoi(e) : 0;
 }
 constexpr int SWEEP_MAX_RHS = 8;             // right-hand sides of the persistent sweeps (k_sweep)
+// Polls after which a wait of the persistent sweeps gives up (environment
+// WCS_SWEEP_POLLS, read by every solve; default SW_POLLS, about two seconds)
+int32_t sweep_polls()
+{
+    const char *e = std::getenv("WCS_SWEEP_POLLS");
+    int32_t v = e ? std::atoi(e) : SW_POLLS;
+    return v > 0 ? v : SW_POLLS;
+}
 constexpr int kPartBlocks = 512;             // blocks of the two-pass column reductions
 
 // Leaf fronts whose pivot columns fit in LDS are factored by one persistent
@@ -828,7 +836,7 @@ struct Layout {
         Br = seg(n * k * 8);
         size_t nseg = nseg_of(S);
         vec = seg((2 * nseg * k + 2 * (size_t)k) * 8 + 64);
-        bad = seg(64);
+        bad = seg(64);     // [0] first bad pivot, [1] a sweep gave up (k_sweep)
         front_off = seg((ns + 1) * 8);
         mfront = seg(ns * 4);
         pfront = seg(ns * 4);
@@ -1505,6 +1513,8 @@ int launch_sweep(wcs_factor f, int part, int k, hipStream_t st)
     a.ex = f->at<T>(Lo.swx);
     a.nk = (int64_t)f->S->n * k;
     a.ctl = reinterpret_cast<int32_t *>(a.ex + 4 * a.nk);
+    a.gave_up = f->at<int32_t>(Lo.bad) + 1;
+    a.polls = sweep_polls();
     a.k = k;
     a.part_l = part == WCS_SOLVE_L;
     a.from_z = part == WCS_SOLVE_FULL;
@@ -1519,6 +1529,20 @@ int launch_sweep(wcs_factor f, int part, int k, hipStream_t st)
     hipLaunchKernelGGL((k_sweep<T, KT>), dim3((unsigned)std::min(a.t1 - a.t0, sweep_per_cu<T, KT>() * f->ncu)), dim3(THREADS), 0, st, a);
     HIP_TRY(hipGetLastError());
     return WCS_OK;
+}
+
+// Whether a sweep of this factor has given up since the last call (waits for
+// the stream; reported once)
+int check_sweeps(wcs_factor f, hipStream_t st)
+{
+    int32_t h = 0;
+    HIP_TRY(hipMemcpyAsync(&h, f->at<int32_t>(f->lay.bad) + 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (!h) return WCS_OK;
+    hipLaunchKernelGGL(k_fill<int32_t>, dim3(1), dim3(64), 0, st, f->at<int32_t>(f->lay.bad) + 1, (int64_t)1, 0);
+    HIP_TRY(hipGetLastError());
+    set_error("a triangular sweep of an earlier solve gave up waiting for a result: its solution holds NaN");
+    return WCS_EHIP;
 }
 
 template <typename T>
@@ -1843,6 +1867,7 @@ int refine_pivot(wcs_factor f, int k, double tol, int max_iter, wcs_ir_report *r
             return WCS_OK;
         };
         rc = residual_norms();
+        if (!rc && worst != worst) rc = check_sweeps(f, st);
         if (rc) return rc;
         // an updated residual that passes the test by less than a factor 100
         // is formed once more from the iterate itself (R = Bp - C Xp, FP64
@@ -2179,6 +2204,8 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
     rc = rc ? rc : upload(f, L.glong, P.glong, st);
     std::vector<int32_t> segp = S.seg_ptr.size() >= 2 ? S.seg_ptr : std::vector<int32_t>{0, S.n};
     rc = rc ? rc : upload(f, L.segp, segp, st);
+    const std::vector<int32_t> status{INT32_MAX, 0};
+    rc = rc ? rc : upload(f, L.bad, status, st);
     if (rc == WCS_OK) {
         hipError_t e = hipStreamSynchronize(st);   // host vectors are pageable: finish the copies
         if (e != hipSuccess) {
@@ -2257,22 +2284,22 @@ int wcs_factor_check(wcs_factor f, wcs_stream stream, int32_t *bad_col)
 {
     if (!f || !bad_col) { set_error("invalid argument to wcs_factor_check"); return WCS_EINVAL; }
     if (!f->have_values) { set_error("no numeric factorization yet"); return WCS_ESTATE; }
-    int32_t h = INT32_MAX;
-    HIP_TRY(hipMemcpyAsync(&h, f->ws + f->lay.bad, sizeof(int32_t), hipMemcpyDeviceToHost, (hipStream_t)stream));
+    int32_t h[2] = {INT32_MAX, 0};
+    HIP_TRY(hipMemcpyAsync(h, f->ws + f->lay.bad, sizeof(h), hipMemcpyDeviceToHost, (hipStream_t)stream));
     HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
-    if (h != INT32_MAX) {
-        *bad_col = h;
+    if (h[0] != INT32_MAX) {
+        *bad_col = h[0];
         if (is_lu(f->prec)) {
-            set_error("zero or non-finite pivot in the LU factorization: pivot " + std::to_string(h) +
-                      " (original index " + std::to_string(f->S->perm[h]) + ")");
+            set_error("zero or non-finite pivot in the LU factorization: pivot " + std::to_string(h[0]) +
+                      " (original index " + std::to_string(f->S->perm[h[0]]) + ")");
             return WCS_ESINGULAR;
         }
-        set_error("matrix is not positive definite: pivot " + std::to_string(h) + " (original index " +
-                  std::to_string(f->S->perm[h]) + ")");
+        set_error("matrix is not positive definite: pivot " + std::to_string(h[0]) + " (original index " +
+                  std::to_string(f->S->perm[h[0]]) + ")");
         return WCS_ENOTSPD;
     }
     *bad_col = -1;
-    return WCS_OK;
+    return h[1] ? check_sweeps(f, (hipStream_t)stream) : WCS_OK;
 }
 
 int wcs_factor_profile_levels(wcs_factor f, const double *values_dev, wcs_stream stream, wcs_kernel_stat *levels)

@@ -19,7 +19,8 @@
 // and waits for nothing, so the launch finishes however few workgroups are
 // resident.  Every wait is bounded all the same: a workgroup that polls too
 // often raises an abort word, which ends all waits and turns what is
-// published from then on into NaN.
+// published from then on into NaN, and the factor's give-up word, from which
+// the host reports it.
 //
 // Exchanged values are written and read with relaxed device-scope atomics,
 // which are coherent across the eight dies' caches, and a value is its own
@@ -64,7 +65,7 @@ struct SweepItem {
 };
 
 constexpr int SW_ROWS = 256;        // update rows per task
-constexpr int SW_SPIN_MAX = 1 << 21;   // polls of about a microsecond
+constexpr int SW_POLLS = 1 << 21;   // polls, of about a microsecond, before a wait gives up
 
 template <typename T> struct SweepArgs {
     const SweepTask *tasks;
@@ -76,6 +77,8 @@ template <typename T> struct SweepArgs {
     T *ex;                          // exchange arrays of n x k each: z, w (forward), v, x (backward)
     int64_t nk;
     int32_t *ctl;                   // [0] queue position, [1] abort
+    int32_t *gave_up;               // set to 1 when a wait gives up; cleared by the host
+    int32_t polls;                  // ... after this many polls
     int32_t t0, t1, k;              // tasks [t0, t1)
     int32_t part_l, from_z;         // Y takes the forward result; the backward sweep starts from it (else from Y)
 };
@@ -149,8 +152,9 @@ template <typename T, int KT> struct Sweep {
     __device__ __forceinline__ bool stuck(int spin)
     {
         __builtin_amdgcn_s_sleep(1);
-        if ((spin & 1023) != 0 || (spin < SW_SPIN_MAX && ld_dev(a.ctl + 1) == SW_UNSET)) return false;
+        if (spin < a.polls && ((spin & 1023) != 0 || ld_dev(a.ctl + 1) == SW_UNSET)) return false;
         st_dev(a.ctl + 1, 1);
+        st_dev(a.gave_up, 1);
         sh.abort = 1;
         return true;
     }

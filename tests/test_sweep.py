@@ -17,6 +17,7 @@ from tests.test_gpu_parity import CASES, dev, prepared
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
+from paper_2007_01541_amd.capi import WcsError  # noqa: E402
 from paper_2007_01541_amd import FP32, FP64, SOLVE_FULL, SOLVE_L, SOLVE_LT, Factor, Symbolic  # noqa: E402
 
 
@@ -100,3 +101,34 @@ def test_forward_sweep_rounds_the_diagonal_term_once(n):
         err = np.abs(X - Z[:, :k])
         print(f"n={n} k={k} largest error {float((err / np.abs(Z[:, :k])).max() / u):.2f} u", flush=True)
         assert np.all(err <= bound[:, :k]), k
+
+
+def test_a_sweep_that_gives_up_is_reported(monkeypatch):
+    """With one poll per wait every sweep gives up (and every workgroup still
+    ends): the solution holds NaN, the next status read reports it, once, and a
+    solve afterwards is the one before."""
+    m, sym, _ = prepared("small")
+    v = dev(m["values"])
+    b = dev(normal_rhs(m["n"], 8, 94))
+    for prec in (FP64, FP32):
+        f = Factor(sym, prec, max_nrhs=8)
+        f.numeric(v)
+        for k in (1, 4, 8):
+            X = f.solve(b[:, :k])
+            assert torch.isfinite(X).all()
+            monkeypatch.setenv("WCS_SWEEP_POLLS", "1")
+            print(f"prec={prec} k={k}", flush=True)
+            assert torch.isnan(f.solve(b[:, :k])).any()
+            with pytest.raises(WcsError) as e:
+                f.pivot_check()
+            assert e.value.code == -3 and "gave up" in str(e.value)
+            assert f.pivot_check() == -1
+            f.solve(b[:, :k])
+            with pytest.raises(WcsError):
+                f.numeric(v)
+            with pytest.raises(WcsError) as e:
+                f.solve_refined(b[:, :k], v)
+            assert e.value.code == -3
+            monkeypatch.delenv("WCS_SWEEP_POLLS")
+            f.numeric(v)
+            assert torch.equal(f.solve(b[:, :k]), X)
