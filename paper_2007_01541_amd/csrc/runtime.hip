@@ -77,7 +77,14 @@ int32_t solve_step_min_rows()
     const char *e = std::getenv("WCS_SOLVE_STEP_ROWS");
     return e ? std::atoi(e) : 0;
 }
-constexpr int SWEEP_MAX_RHS = 8;             // right-hand sides of the persistent sweeps (k_sweep)
+// Right-hand sides of the persistent sweeps (k_sweep): all that its widest form
+// takes.  One solve, level by level and persistent, us: N = 1,024 FP64, 1 / 5 / 8
+// right-hand sides 276 / 490 / 511 and 39 / 157 / 163; N = 11,470 FP32 617 / 849
+// / 747 and 164 / 366 / 375; N = 65,536 (a = 2) FP64 2218 / 4429 / 4410 and 567 /
+// 1538 / 1740, FP32 1884 / 2911 / 2474 and 403 / 952 / 1038; N = 262,144 FP64
+// 5999 / 13947 / 13480 and 2262 / 4967 / 5267, FP32 4422 / 7900 / 6621 and 1482
+// / 2925 / 3086; 2-4, 6, 7 and LU lie between.  Faster at every count up to 8.
+constexpr int SWEEP_MAX_RHS = 8;
 // Polls after which a wait of the persistent sweeps gives up (environment
 // WCS_SWEEP_POLLS, read by every solve; default SW_POLLS, about two seconds)
 int32_t sweep_polls()
@@ -112,10 +119,11 @@ int side_grid(int ncu)
 }
 
 // Right-hand-side counts from 5 up to this one run the 16-column sweep
-// kernels, larger ones the 64-column ones (environment WCS_SOLVE_KT16_MAX,
-// read by every solve; default 4: none).  Measured at N = 2^18, one solve:
-// 8 RHS FP32 11.7 ms with the 16-column kernels, 7.0 ms with the 64-column
-// ones; 16 RHS 12.2 / 7.1 ms; FP64 16 RHS 22.1 / 14.4 ms.
+// kernels level by level (environment WCS_SOLVE_KT16_MAX, read by every solve;
+// default 4: none).  Otherwise 5..SWEEP_MAX_RHS take the persistent sweep and
+// larger counts the 64-column kernels.  Measured at N = 2^18, one solve: 8 RHS
+// FP32 11.7 ms with the 16-column kernels, 6.6 ms with the 64-column ones, 3.1
+// ms with the sweep; 16 RHS 12.2 / 6.7 ms; FP64 16 RHS 22.1 / 13.8 ms.
 int kt16_max_rhs()
 {
     const char *e = std::getenv("WCS_SOLVE_KT16_MAX");
@@ -1548,7 +1556,7 @@ int check_sweeps(wcs_factor f, hipStream_t st)
 template <typename T>
 int launch_solve_internal(wcs_factor f, int part, int k, hipStream_t st)
 {
-    if (f->plan.sw_ok && k <= SWEEP_MAX_RHS) {
+    if (f->plan.sw_ok && k <= SWEEP_MAX_RHS && (k <= 4 || k > kt16_max_rhs())) {
         if (k == 1) return launch_sweep<T, 1>(f, part, k, st);
         if (k <= 4) return launch_sweep<T, 4>(f, part, k, st);
         return launch_sweep<T, 8>(f, part, k, st);
