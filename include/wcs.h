@@ -241,9 +241,11 @@ int wcs_factor_export_upper(wcs_factor f, int32_t j0, int32_t j1, int64_t *Up, i
  * no look-ahead or auxiliary stream).  The static array belongs to the
  * current device and serves one factor at a time: WCS_ESTATE while another
  * factor created by this call on the same device is alive (wcs_factor_free
- * releases it), WCS_ENOMEM (with the needed size in wcs_last_error) when
- * wcs_workspace_size for sym, prec and max_nrhs exceeds
- * WCS_STATIC_WORKSPACE_BYTES.  The array keeps the last factor's contents;
+ * releases it), WCS_ENOMEM (with the needed size in wcs_last_error) when the
+ * system does not fit in WCS_STATIC_WORKSPACE_BYTES.  Where it fits but for
+ * the tables of the one-launch solves of few right-hand sides (up to 2% of
+ * wcs_workspace_size), the factor does without them and solves those level by
+ * level: the same accuracy in another order of summation.  The array keeps the last factor's contents;
  * every numeric factorization clears what it needs.  Calls on such a factor
  * that overlap in time on one GPU (different streams or threads) race.
  * All other calls take the factor as they take one from wcs_factor_create and

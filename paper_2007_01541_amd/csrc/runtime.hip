@@ -262,6 +262,14 @@ struct Plan {
     int64_t sw_fwd = 0;
     bool sw_ok = false;
 
+    void drop_sweep()
+    {
+        sw_ok = false;
+        sw_fwd = 0;
+        std::vector<SweepTask>().swap(sw_tasks);
+        std::vector<SweepItem>().swap(sw_items);
+    }
+
     // needs the solve schedule (xoff, sbsum_tasks) of every front
     void build_sweep(const Symbolic &S, const std::vector<std::vector<int32_t>> &bylev)
     {
@@ -903,7 +911,7 @@ struct Layout {
         diagf = seg(std::max<size_t>(1, P.diag_fronts.size()) * 4);
         stept = seg(std::max<size_t>(1, P.step_tasks.size()) * sizeof(int4));
         swt = seg(P.sw_tasks.size() * sizeof(SweepTask));
-        glong = seg(std::max<size_t>(1, P.glong.size()) * 4);
+        glong = seg(P.glong.size() * 4);
         swi = seg(P.sw_items.size() * sizeof(SweepItem));
         // exchange arrays (z, w, v, x), then ctl
         swx = seg(P.sw_ok ? (size_t)4 * n * std::min(k, SWEEP_MAX_RHS) * esz + 16 : 0);
@@ -2019,8 +2027,10 @@ int wcs_workspace_size(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, s
 
 namespace wcs {
 namespace {
-// Plan and layout of a new factor (host only).
-int new_factor(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, wcs_factor *fp)
+// Plan and layout of a new factor (host only).  The persistent sweeps' tables
+// and exchange arrays are left out where they alone exceed limit bytes (few
+// right-hand sides are then solved level by level).
+int new_factor(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, size_t limit, wcs_factor *fp)
 {
     wcs_factor f = new (std::nothrow) wcs_factor_s;
     if (!f) return WCS_ENOMEM;
@@ -2032,6 +2042,10 @@ int new_factor(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, wcs_facto
         if (narrow_src(*f->S)) f->plan.src32.assign(f->S->csr_src.begin(), f->S->csr_src.end());
         for (Level &L : f->plan.levels) L.upd_var = default_update_variant(prec);
         f->lay.compute(*f->S, f->plan, elem_size(prec), max_nrhs, is_lu(prec));
+        if (f->lay.total > limit) {
+            f->plan.drop_sweep();
+            f->lay.compute(*f->S, f->plan, elem_size(prec), max_nrhs, is_lu(prec));
+        }
     } catch (const std::bad_alloc &) {
         delete f;
         set_error("host allocation failed");
@@ -2062,7 +2076,7 @@ int wcs_factor_create(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, vo
     }
     *out = nullptr;
     wcs_factor f = nullptr;
-    int rc = new_factor(sym, prec, max_nrhs, &f);
+    int rc = new_factor(sym, prec, max_nrhs, SIZE_MAX, &f);
     if (rc) return rc;
     if (bytes < f->lay.total) {
         set_error("workspace too small: need " + std::to_string(f->lay.total) + " bytes, got " + std::to_string(bytes));
@@ -2094,7 +2108,7 @@ int wcs_factor_create_static(wcs_symbolic sym, wcs_precision prec, int32_t max_n
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     wcs_factor f = nullptr;
-    int rc = new_factor(sym, prec, max_nrhs, &f);
+    int rc = new_factor(sym, prec, max_nrhs, (size_t)WCS_STATIC_WORKSPACE_BYTES, &f);
     if (rc) return rc;
     if (f->lay.total > (size_t)WCS_STATIC_WORKSPACE_BYTES) {
         set_error("static workspace too small: this system needs " + std::to_string(f->lay.total) +

@@ -80,3 +80,27 @@ def test_static_factor_one_per_device_and_size_limit():
     rc = capi.lib().wcs_factor_create_static(sb.handle, FP64, 1, None, C.byref(h))
     assert rc == -2 and not h.value
     assert "static workspace too small" in capi.lib().wcs_last_error().decode()
+
+
+@pytest.mark.parametrize("k", [1, 4, 8])
+def test_static_factor_without_room_for_the_sweep_tables(k):
+    """A tridiagonal system whose factor fits in the static array but for the
+    tables and exchange arrays of the one-launch solves: it is accepted and
+    solves level by level (entries of the inverse decay by 0.27 per step, so
+    every sum has a few terms: a residual of less than 45 eps max |b|)."""
+    n = 4272
+    colptr = np.concatenate([2 * np.arange(n), [2 * n - 1]]).astype(np.int64)
+    rowind = np.stack([np.arange(n), np.arange(n) + 1], 1).ravel()[:-1].astype(np.int32)
+    sym = Symbolic(n, colptr, rowind)
+    assert 0 < sym.workspace_size(FP64, 8) - STATIC_BYTES < STATIC_BYTES // 50
+    values = np.full(2 * n - 1, -1.0)
+    values[0::2] = 4.0
+    f = Factor(sym, FP64, max_nrhs=8, static_workspace=True)
+    f.numeric(dev(values))
+    B = normal_rhs(n, k, 96)
+    X = f.solve(dev(B)).cpu().numpy().reshape(n, -1)
+    R = B.reshape(n, -1) - 4.0 * X
+    R[:-1] += X[1:]
+    R[1:] += X[:-1]
+    print(f"n={n} k={k}", flush=True)
+    assert np.abs(R).max() <= 1e-14 * np.abs(B).max()
