@@ -653,7 +653,7 @@ int analyze(int32_t n, const int64_t *colptr, const int32_t *rowind, const wcs_a
         }
     }
     // full symmetric CSR of C = P A P^T (pivot order, columns ascending) for
-    // the refinement residual; csr_src names the stored entry of each value
+    // the refinement residual; csr_src32 or csr_src names the stored entry of each value
     S.csr_ptr.assign((size_t)n + 1, 0);
     for (int32_t j = 0; j < n; j++)
         for (int64_t p = colptr[j]; p < colptr[j + 1]; p++) {
@@ -663,32 +663,35 @@ int analyze(int32_t n, const int64_t *colptr, const int32_t *rowind, const wcs_a
         }
     for (int32_t i = 0; i < n; i++) S.csr_ptr[i + 1] += S.csr_ptr[i];
     S.csr_col.resize((size_t)S.csr_ptr[n]);
-    S.csr_src.resize((size_t)S.csr_ptr[n]);
-    {
+    auto fill_csr = [&](auto &src) {
+        typedef typename std::decay<decltype(src[0])>::type I;
+        src.resize((size_t)S.csr_ptr[n]);
         std::vector<int64_t> fill(S.csr_ptr.begin(), S.csr_ptr.end() - 1);
         for (int32_t j = 0; j < n; j++)
             for (int64_t p = colptr[j]; p < colptr[j + 1]; p++) {
                 int32_t i = rowind[p];
                 int32_t a = S.iperm[i], b = S.iperm[j];
                 S.csr_col[fill[a]] = b;
-                S.csr_src[fill[a]++] = p;
+                src[fill[a]++] = (I)p;
                 if (i != j) {
                     S.csr_col[fill[b]] = a;
-                    S.csr_src[fill[b]++] = p;
+                    src[fill[b]++] = (I)p;
                 }
             }
-        std::vector<std::pair<int32_t, int64_t>> tmp2;
+        std::vector<std::pair<int32_t, I>> tmp2;
         for (int32_t r = 0; r < n; r++) {
             int64_t a = S.csr_ptr[r], b = S.csr_ptr[r + 1];
             tmp2.resize((size_t)(b - a));
-            for (int64_t q = a; q < b; q++) tmp2[q - a] = {S.csr_col[q], S.csr_src[q]};
+            for (int64_t q = a; q < b; q++) tmp2[q - a] = {S.csr_col[q], src[q]};
             std::sort(tmp2.begin(), tmp2.end());
             for (int64_t q = a; q < b; q++) {
                 S.csr_col[q] = tmp2[q - a].first;
-                S.csr_src[q] = tmp2[q - a].second;
+                src[q] = tmp2[q - a].second;
             }
         }
-    }
+    };
+    if (S.csr_ptr[n] <= INT32_MAX) fill_csr(S.csr_src32);
+    else fill_csr(S.csr_src);
     S.seg_ptr = {0, n};
     return WCS_OK;
 }
@@ -738,7 +741,8 @@ int combine(int32_t count, const Symbolic *const *parts, Symbolic &S)
     S.amap.resize((size_t)nnz_tot);
     S.csr_ptr.resize((size_t)n_tot + 1);
     S.csr_col.resize((size_t)csr_tot);
-    S.csr_src.resize((size_t)csr_tot);
+    if (csr_tot <= INT32_MAX) S.csr_src32.resize((size_t)csr_tot);
+    else S.csr_src.resize((size_t)csr_tot);
     S.seg_ptr.resize((size_t)count + 1);
     S.colptr[0] = 0;
     S.fund_ptr[0] = 0;
@@ -806,10 +810,13 @@ int combine(int32_t count, const Symbolic *const *parts, Symbolic &S)
             S.rows[roff + q] = P.rows[q] + noff;
             S.rel[roff + q] = P.rel[q];
         }
-        for (size_t q = 0; q < P.csr_col.size(); q++) {
-            S.csr_col[coff + q] = P.csr_col[q] + noff;
-            S.csr_src[coff + q] = P.csr_src[q] + zoff;
-        }
+        for (size_t q = 0; q < P.csr_col.size(); q++) S.csr_col[coff + q] = P.csr_col[q] + noff;
+        // a union of at most INT32_MAX entries has no part of more
+        for (size_t q = 0; q < P.csr_src32.size() && !S.csr_src32.empty(); q++)
+            S.csr_src32[coff + q] = P.csr_src32[q] + (int32_t)zoff;
+        for (size_t q = 0; q < P.csr_src32.size() && !S.csr_src.empty(); q++)
+            S.csr_src[coff + q] = P.csr_src32[q] + zoff;
+        for (size_t q = 0; q < P.csr_src.size(); q++) S.csr_src[coff + q] = P.csr_src[q] + zoff;
     };
     unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     nth = std::min<unsigned>(nth, (unsigned)count);

@@ -47,9 +47,12 @@ struct Symbolic {
     std::vector<int64_t> amap;       // per stored entry: element offset inside the fronts
 
     // full symmetric CSR of P A P^T in pivot order (for the residual), with
-    // the stored-entry index each CSR entry takes its value from
+    // the stored-entry index each CSR entry takes its value from: in csr_src32
+    // when there are at most INT32_MAX entries, else in csr_src (the other one
+    // is empty)
     std::vector<int64_t> csr_ptr;
     std::vector<int32_t> csr_col;
+    std::vector<int32_t> csr_src32;
     std::vector<int64_t> csr_src;
 
     // independent diagonal blocks (instances of a batch): block b holds the

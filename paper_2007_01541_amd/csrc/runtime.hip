@@ -52,8 +52,8 @@ int expand_side_blocks()
     return b > 0 ? b : 256;
 }
 
-// the value expansion's source indices fit 32 bits (they are in [0, stored entries))
-bool narrow_src(const Symbolic &S) { return S.csr_src.size() <= (size_t)INT32_MAX; }
+// the value expansion's source indices are held in 32 bits
+bool narrow_src(const Symbolic &S) { return S.csr_src.empty(); }
 
 size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
@@ -257,7 +257,6 @@ struct Plan {
     int32_t nbo = 512;                            // outer block of this plan
     // persistent sweeps for few right-hand sides (k_sweep): forward tasks, then backward ones
     std::vector<SweepTask> sw_tasks;
-    std::vector<int32_t> src32;                // Symbolic::csr_src where it fits, until it is uploaded
     std::vector<SweepItem> sw_items;
     int64_t sw_fwd = 0;
     bool sw_ok = false;
@@ -869,7 +868,7 @@ struct Layout {
         perm = seg(n * 4);
         csr_ptr = seg((n + 1) * 8);
         csr_col = seg(S.csr_col.size() * 4);
-        csr_src = seg(S.csr_src.size() * (narrow_src(S) ? 4 : 8));
+        csr_src = seg(S.csr_src32.size() * 4 + S.csr_src.size() * 8);
         csr_val = seg(S.csr_col.size() * 8);
         rowind = seg((size_t)S.nnz * 4);
         colof = seg((size_t)S.nnz * 4);
@@ -2039,7 +2038,6 @@ int new_factor(wcs_symbolic sym, wcs_precision prec, int32_t max_nrhs, size_t li
         f->prec = prec;
         f->max_nrhs = max_nrhs;
         f->plan.build(*f->S, elem_size(prec), prec != WCS_LU64 && leaf_kernel_enabled(), prec != WCS_LU64);
-        if (narrow_src(*f->S)) f->plan.src32.assign(f->S->csr_src.begin(), f->S->csr_src.end());
         for (Level &L : f->plan.levels) L.upd_var = default_update_variant(prec);
         f->lay.compute(*f->S, f->plan, elem_size(prec), max_nrhs, is_lu(prec));
         if (f->lay.total > limit) {
@@ -2176,10 +2174,8 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
     rc = rc ? rc : upload(f, L.perm, S.perm, st);
     rc = rc ? rc : upload(f, L.csr_ptr, S.csr_ptr, st);
     rc = rc ? rc : upload(f, L.csr_col, S.csr_col, st);
-    if (narrow_src(S))
-        rc = rc ? rc : upload(f, L.csr_src, P.src32, st);
-    else
-        rc = rc ? rc : upload(f, L.csr_src, S.csr_src, st);
+    rc = rc ? rc : upload(f, L.csr_src, S.csr_src32, st);
+    rc = rc ? rc : upload(f, L.csr_src, S.csr_src, st);
     rc = rc ? rc : upload(f, L.spchunk, f->plan.spmv_chunks, st);
     rc = rc ? rc : upload(f, L.splong, f->plan.spmv_long, st);
     rc = rc ? rc : upload(f, L.spgrp, f->plan.spmv_grp, st);
@@ -2236,7 +2232,6 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
         }
     }
     if (rc) { delete f; return rc; }
-    std::vector<int32_t>().swap(f->plan.src32);
     *out = f;
     return WCS_OK;
 }
