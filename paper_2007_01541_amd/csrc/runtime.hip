@@ -1663,8 +1663,8 @@ int launch_apply(wcs_factor f, int part, int k, double *B, int64_t ld, hipStream
         // short contractions by a wave per tile (its vector accesses need k a multiple of 4)
         const int64_t nt = (int64_t)P.al_tasks.size(), nl = k % 4 == 0 ? P.al_long : nt;
         if (P.al_strip)
-            hipLaunchKernelGGL(k_apply_l_strip<T>, dim3((unsigned)P.al_strip, (unsigned)((k + 15) / 16)), dim3(THREADS),
-                               0, st, f->at<int2>(Lo.alt2), a, (const T *)Y, W);
+            hipLaunchKernelGGL(k_apply_l_strip<T>, dim3((unsigned)P.al_strip, (unsigned)std::min((k + 15) / 16, APPLY_STRIPS)),
+                               dim3(THREADS), 0, st, f->at<int2>(Lo.alt2), a, (const T *)Y, W);
         if (nl > P.al_strip)
             hipLaunchKernelGGL(k_apply_l<T>, dim3((unsigned)(nl - P.al_strip)), dim3(THREADS), 0, st,
                                f->at<int2>(Lo.alt2) + P.al_strip, a, (const T *)Y, W);

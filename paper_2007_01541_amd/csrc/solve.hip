@@ -1507,6 +1507,7 @@ __global__ __launch_bounds__(THREADS, sizeof(T) == 4 ? 3 : 2) void k_apply_lt(co
 }
 
 constexpr int APPLY_WAVE_K = 128, APPLY_STRIP_K = 1024;
+constexpr int APPLY_STRIPS = 64;        // most strips of a tile in one launch (grid y)
 
 // L Y, first pass: task = (front, 64-row tile).  W row woff[f] + r of the
 // front's own row block gets sum over its pivot columns c <= r of
@@ -1551,7 +1552,7 @@ __global__ __launch_bounds__(THREADS, sizeof(T) == 4 ? 3 : 2) void k_apply_l(con
 }
 
 // The same for tiles of more than APPLY_STRIP_K pivot columns: task = (front,
-// 64-row tile), grid y = 16 columns of the right-hand sides.  The few tiles of
+// 64-row tile), grid y = strip of 16 columns of the right-hand sides.  The few tiles of
 // a large separator have thousands of pivot columns each and their time is
 // that of one workgroup's chain of loads: the strips give four times the
 // workgroups and 64 pivot columns of L in flight per wave.  They also read L
@@ -1572,41 +1573,45 @@ __global__ __launch_bounds__(THREADS, 2) void k_apply_l_strip(const int2 *__rest
     T *out = W + a.woff[f] * k;
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, kq = lane / 16, ln = lane % 16;
     const int per = ((kend + 63) / 64) * 16, cb0 = wave * per, ce = min(kend, cb0 + per);
-    const int col = blockIdx.y * 16 + ln;
-    V acc[4];
+    // grid y is bounded, so a workgroup may take several strips
+    for (int s0 = blockIdx.y * 16; s0 < k; s0 += gridDim.y * 16) {
+        const int col = s0 + ln;
+        V acc[4];
 #pragma unroll
-    for (int x = 0; x < 4; x++)
+        for (int x = 0; x < 4; x++)
 #pragma unroll
-        for (int e = 0; e < 4; e++) acc[x][e] = 0;
-    for (int kg = cb0; kg < ce; kg += 64) {
-        T av[16][4], bv[16];
-        const bool edge = kg + 64 > ce || kg + 64 > r0 || r0 + 64 > m;     // columns past the end, or above the diagonal
+            for (int e = 0; e < 4; e++) acc[x][e] = 0;
+        for (int kg = cb0; kg < ce; kg += 64) {
+            T av[16][4], bv[16];
+            const bool edge = kg + 64 > ce || kg + 64 > r0 || r0 + 64 > m;     // columns past the end, or above the diagonal
 #pragma unroll
-        for (int s = 0; s < 16; s++) {
-            const int c = kg + 4 * s + kq;
-            bv[s] = c < ce && col < k ? Yin[(int64_t)(first + c) * k + col] : (T)0;
+            for (int s = 0; s < 16; s++) {
+                const int c = kg + 4 * s + kq;
+                bv[s] = c < ce && col < k ? Yin[(int64_t)(first + c) * k + col] : (T)0;
 #pragma unroll
-            for (int x = 0; x < 4; x++) {
-                const int r = r0 + 16 * x + ln;
-                if (!edge) av[s][x] = L[(int64_t)c * ld + r];
-                else av[s][x] = (c < ce && r < m && c <= r) ? L[(int64_t)c * ld + r] : (T)0;
+                for (int x = 0; x < 4; x++) {
+                    const int r = r0 + 16 * x + ln;
+                    if (!edge) av[s][x] = L[(int64_t)c * ld + r];
+                    else av[s][x] = (c < ce && r < m && c <= r) ? L[(int64_t)c * ld + r] : (T)0;
+                }
             }
+#pragma unroll
+            for (int s = 0; s < 16; s++)
+#pragma unroll
+                for (int x = 0; x < 4; x++) acc[x] = Mfma<T>::mma(av[s][x], bv[s], acc[x]);
         }
+        if (s0 != (int)blockIdx.y * 16) __syncthreads();     // the last strip's sums are read
 #pragma unroll
-        for (int s = 0; s < 16; s++)
+        for (int x = 0; x < 4; x++)
 #pragma unroll
-            for (int x = 0; x < 4; x++) acc[x] = Mfma<T>::mma(av[s][x], bv[s], acc[x]);
-    }
+            for (int e = 0; e < 4; e++) red[(wave * 64 + 16 * x + Mfma<T>::row(kq, e)) * 16 + ln] = acc[x][e];
+        __syncthreads();
 #pragma unroll
-    for (int x = 0; x < 4; x++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) red[(wave * 64 + 16 * x + Mfma<T>::row(kq, e)) * 16 + ln] = acc[x][e];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int e = tid + THREADS * q, r = r0 + e / 16, c = blockIdx.y * 16 + e % 16;
-        if (r < m && c < k)
-            out[(int64_t)r * k + c] = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
+        for (int q = 0; q < 4; q++) {
+            const int e = tid + THREADS * q, r = r0 + e / 16, c = s0 + e % 16;
+            if (r < m && c < k)
+                out[(int64_t)r * k + c] = (red[e] + red[1024 + e]) + (red[2048 + e] + red[3072 + e]);
+        }
     }
 }
 

@@ -37,3 +37,22 @@ def test_product_tiles(prec):
         ref = oracle.apply(ex["perm"], Lp, Li, Lx, B, APPLY_L)
         bound = (n + 2) * eps * oracle.apply(ex["perm"], Lp, Li, np.abs(Lx), np.abs(B), APPLY_L)
         assert np.all(np.abs(X - ref) <= bound), k
+
+
+def test_product_of_more_strips_than_one_launch_takes():
+    """A dense front of 1,100 pivots and 1,041 right-hand sides: 66 strips of 16
+    columns, more than the 64 of a launch (whose grid is bounded in y), the last
+    of one column; bitwise the product of the columns taken a few at a time."""
+    n, k = 1100, 1041
+    rng = np.random.default_rng(7)
+    G = rng.uniform(-1.0, 1.0, (n, n))
+    G[np.diag_indices(n)] = n
+    colptr = np.concatenate([[0], np.cumsum(n - np.arange(n))]).astype(np.int64)
+    rowind = np.concatenate([np.arange(c, n) for c in range(n)]).astype(np.int32)
+    f = Factor(Symbolic(n, colptr, rowind, leaf_size=n, dense_degree_min=4 * n), FP64, max_nrhs=k)
+    f.numeric(dev(np.concatenate([G[c:, c] for c in range(n)])))
+    B = dev(normal_rhs(n, k, 97))
+    X = f.apply(B, APPLY_L)
+    for c in (0, 1008, 1024, 1040):
+        print(f"columns from {c}", flush=True)
+        assert torch.equal(f.apply(B[:, c:c + 17], APPLY_L), X[:, c:c + 17]), c
