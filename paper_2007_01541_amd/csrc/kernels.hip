@@ -50,9 +50,21 @@ __global__ void k_zero_lower(const int2 *__restrict__ tasks, const int64_t *__re
 // Passes over the matrix entries give every XCD a contiguous eighth of them, in
 // chunks of XCD_CHUNK taken by consecutive workgroups of that XCD (workgroups
 // go to the XCDs round robin), so that lines which neighbouring rows or columns
-// share are read or filled through one L2.  The grid is a multiple of XCDS.
+// share are read or filled through one L2.  The grid is a multiple of XCDS, or
+// smaller than XCDS: then every workgroup takes a range of its own.
 constexpr int XCDS = 8;
 constexpr int XCD_CHUNK = 256 * 8;
+struct XcdShare {
+    int64_t begin, end;     // this workgroup's chunks: begin, begin + step, ... < end
+    int step;
+    __device__ __forceinline__ explicit XcdShare(int64_t chunks)
+    {
+        const int nx = min((int)gridDim.x, XCDS), x = blockIdx.x % nx;
+        step = gridDim.x / nx;
+        begin = chunks * x / nx + blockIdx.x / nx;
+        end = chunks * (x + 1) / nx;
+    }
+};
 
 // fronts[amap[e]] = values[e]: the stored entries of A into their fronts.  Bound
 // by partly written lines: a column's entries fall into runs of a front column.
@@ -64,9 +76,8 @@ __global__ __launch_bounds__(256) void k_scatter(const double *__restrict__ valu
 {
     constexpr int U = XCD_CHUNK / 256;   // loads of U entries before their stores
     const int64_t nch = (nnz + XCD_CHUNK - 1) / XCD_CHUNK;
-    const int xcd = blockIdx.x % XCDS, per = gridDim.x / XCDS;
-    const int64_t end = nch * (xcd + 1) / XCDS;
-    for (int64_t ch = nch * xcd / XCDS + blockIdx.x / XCDS; ch < end; ch += per) {
+    const XcdShare x(nch);
+    for (int64_t ch = x.begin; ch < x.end; ch += x.step) {
         const int64_t i = ch * XCD_CHUNK + threadIdx.x;
         int64_t dst[U];
         T v[U];
@@ -1464,9 +1475,8 @@ __global__ __launch_bounds__(256) void k_expand_values(const double *__restrict_
 {
     constexpr int U = XCD_CHUNK / 256;
     const int64_t nch = (nnz + XCD_CHUNK - 1) / XCD_CHUNK;
-    const int xcd = blockIdx.x % XCDS, per = gridDim.x / XCDS;
-    const int64_t end = nch * (xcd + 1) / XCDS;
-    for (int64_t ch = nch * xcd / XCDS + blockIdx.x / XCDS; ch < end; ch += per) {
+    const XcdShare x(nch);
+    for (int64_t ch = x.begin; ch < x.end; ch += x.step) {
         const int64_t i = ch * XCD_CHUNK + threadIdx.x;
         I s[U];
         double v[U];

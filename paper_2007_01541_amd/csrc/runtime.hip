@@ -42,8 +42,8 @@ int32_t fp64_diag_min_cols()
 }
 
 // Workgroups of the matrix-value expansion when it runs beside the first
-// solve of a refinement (environment WCS_EXPAND_BLOCKS, default 256: one per
-// CU of an MI355X; measured on the 2^18 headline system with 64 right-hand
+// solve of a refinement (environment WCS_EXPAND_BLOCKS, from eight on rounded up
+// to a multiple of eight; default 256: one per CU of an MI355X; measured on the 2^18 headline system with 64 right-hand
 // sides, 128 and 256 are equally fast, 64 and 512 or more slower)
 int expand_side_blocks()
 {
@@ -926,11 +926,11 @@ bool valid_prec(wcs_precision p) { return p == WCS_FP64 || p == WCS_FP32 || p ==
 // is the faster one in FP64 and the register-staged one in FP32.
 int32_t default_update_variant(wcs_precision p) { return p == WCS_FP32 ? WCS_UPD_REG128 : WCS_UPD_STREAM128; }
 
-// grid of a pass by XCD_CHUNK entries: a multiple of XCDS, about `most` at most
+// grid of a pass by XCD_CHUNK entries (XcdShare): `most` at most, from XCDS on rounded up to a multiple of it
 dim3 xcd_grid(int64_t entries, int most)
 {
     const int64_t g = std::clamp<int64_t>((entries + XCD_CHUNK - 1) / XCD_CHUNK, 1, most);
-    return dim3((unsigned)((g + XCDS - 1) / XCDS * XCDS));
+    return dim3((unsigned)(g < XCDS ? g : (g + XCDS - 1) / XCDS * XCDS));
 }
 
 int grid_for(int64_t work, int threads = 256)
