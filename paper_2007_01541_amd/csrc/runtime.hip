@@ -69,9 +69,11 @@ int32_t outer_block()
     int32_t v = e ? std::atoi(e) : 512;
     return v >= 64 && v % 64 == 0 ? v : 512;
 }
-// fronts with more rows solve block by block over many workgroups (tuning knob WCS_SOLVE_STEP_ROWS)
-// Fronts of at most this many rows are solved one workgroup per front for the
-// whole sweep; by default none (the super-block path is faster for them too).
+// Fronts of at most this many rows (environment WCS_SOLVE_STEP_ROWS, read when
+// a plan is built; default 0) are solved one workgroup per front for the whole
+// sweep, the others super-block by super-block over many workgroups; by
+// default all are (the super-block path is faster for small ones too).  A value
+// that catches a front takes the whole factor off the persistent sweeps.
 int32_t solve_step_min_rows()
 {
     const char *e = std::getenv("WCS_SOLVE_STEP_ROWS");
@@ -1568,6 +1570,8 @@ int launch_solve_internal(wcs_factor f, int part, int k, hipStream_t st)
         if (k <= 4) return launch_sweep<T, 4>(f, part, k, st);
         return launch_sweep<T, 8>(f, part, k, st);
     }
+    // up to four columns come here where the plan has no persistent sweep
+    // (WCS_SOLVE_STEP_ROWS, no room in the static workspace, 2^30 tasks)
     if (k <= 4) return launch_sweeps<T, 4>(f, part, k, st);
     if (k <= kt16_max_rhs()) return launch_sweeps<T, 16>(f, part, k, st);
     return launch_sweeps<T, 64>(f, part, k, st);

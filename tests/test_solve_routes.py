@@ -35,3 +35,47 @@ def test_sixteen_column_switch_counts_from_five(prec, monkeypatch):
     monkeypatch.setenv("WCS_SOLVE_KT16_MAX", "4")
     for k in (5, 8):
         assert torch.equal(f.solve(b[:, :k]), default[k]), k
+
+
+@pytest.mark.parametrize("kind,leaf,coords", CASES)
+@pytest.mark.parametrize("rows", ["100000", "64"])
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_fused_fronts_of_few_columns(kind, leaf, coords, rows, prec, monkeypatch):
+    """WCS_SOLVE_STEP_ROWS takes the whole factor off the persistent sweep: the
+    four-column level kernels, all fronts fused or the small ones beside
+    super-block fronts, at the column counts below their width."""
+    monkeypatch.setenv("WCS_SOLVE_STEP_ROWS", rows)
+    m, sym, orc = prepared(kind, leaf, coords)
+    B = normal_rhs(m["n"], 4, 99)
+    f = Factor(sym, prec, max_nrhs=4)
+    f.numeric(dev(m["values"]))
+    tol = factor_tol(m, int(orc.colcount.max()), EPS64 if prec == FP64 else EPS32)
+    for part in (SOLVE_FULL, SOLVE_L, SOLVE_LT):
+        Xo = orc.solve(B, part)
+        for k in (2, 3, 4):
+            print(f"case {kind} rows={rows} prec={prec} part={part} k={k}", flush=True)
+            X = f.solve(dev(B[:, :k]), part).cpu().numpy()
+            assert np.abs(X - Xo[:, :k]).max() <= tol * np.abs(Xo).max(), (part, k)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_super_block_levels_of_few_columns(prec):
+    """The level kernels without fused fronts at the counts that the persistent
+    sweep takes by default: fronts of up to 316 pivots in the static workspace,
+    with so large a max_nrhs that the sweep's tables alone do not fit."""
+    m, sym, orc = prepared(*next(c for c in CASES if c[0] == "g5a13"))
+    limit = 64 << 20
+    lo, hi = 8, 4096
+    while lo + 1 < hi:                       # workspace_size(lo) <= limit < workspace_size(hi)
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if sym.workspace_size(prec, mid) > limit else (mid, hi)
+    f = Factor(sym, prec, max_nrhs=hi, static_workspace=True)
+    f.numeric(dev(m["values"]))
+    B = normal_rhs(m["n"], 8, 100)
+    tol = factor_tol(m, int(orc.colcount.max()), EPS64 if prec == FP64 else EPS32)
+    for part in (SOLVE_FULL, SOLVE_L, SOLVE_LT):
+        Xo = orc.solve(B, part)
+        for k in (1, 2, 3, 4, 5, 8):
+            print(f"max_nrhs={hi} prec={prec} part={part} k={k}", flush=True)
+            X = f.solve(dev(B[:, :k]), part).cpu().numpy()
+            assert np.abs(X - Xo[:, :k]).max() <= tol * np.abs(Xo).max(), (part, k)
