@@ -225,14 +225,15 @@ __device__ __forceinline__ float lane_bcast(float x, int src)
 // 1 / sqrt(d) for a pivot of the diagonal-block factorization: the hardware
 // estimate (relative error below 2^-24 in FP64) and one Newton step, which
 // leaves a few units in the last place (FP64: about 1e-15 relative; FP32: the
-// estimate refined once as well).  FULL: a second step in FP64, to the last
-// place (the leaf kernel: every column starts from a leaf's.  Largest error of
-// sqrt(d) over 4,096 mantissas: 17.9 eps with one step, 1.2 with two).
-template <bool FULL, typename TD> __device__ __forceinline__ TD rsqrt_pivot(TD d)
+// estimate refined once as well).  full: a second step in FP64, to the last
+// place (fronts of one panel, as every leaf: all other columns start from
+// theirs.  Largest error of sqrt(d) over 4,096 mantissas: 17.9 eps with one
+// step, 1.2 with two).
+template <typename TD, typename Full> __device__ __forceinline__ TD rsqrt_pivot(TD d, Full full)
 {
     TD r = sizeof(TD) == 8 ? (TD)__builtin_amdgcn_rsq((double)d) : (TD)__builtin_amdgcn_rsqf((float)d);
     r = r * ((TD)1.5 - (TD)0.5 * d * r * r);
-    if constexpr (FULL && sizeof(TD) == 8) r = r * ((TD)1.5 - (TD)0.5 * d * r * r);
+    if (sizeof(TD) == 8 && full) r = r * ((TD)1.5 - (TD)0.5 * d * r * r);
     return r;
 }
 
@@ -241,9 +242,10 @@ template <bool FULL, typename TD> __device__ __forceinline__ TD rsqrt_pivot(TD d
 // writes fall in distinct banks)
 template <typename TD> using DiagInv = TD[NB / 16][16][17];
 
-template <typename TD, bool FULL = false, typename Slab>
+template <typename TD, typename Slab, typename Full = std::false_type>
 __device__ __forceinline__ void factor_diag_block(TD (&A)[NB][NB + 1], DiagInv<TD> &Iv, TD (&Rd)[NB], int nb,
-                                                  bool report, int32_t *bad, int32_t piv0, Slab slab)
+                                                  bool report, int32_t *bad, int32_t piv0, Slab slab,
+                                                  Full full = Full())
 {
     typedef typename Mfma<TD>::V VD;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -307,14 +309,14 @@ __device__ __forceinline__ void factor_diag_block(TD (&A)[NB][NB + 1], DiagInv<T
                 first_bad = min(first_bad, j);
                 d0 = (TD)1;
             }
-            TD r0 = rsqrt_pivot<FULL>(d0);
+            TD r0 = rsqrt_pivot(d0, full);
             TD l10 = d01 * r0;
             TD e1 = d1 - l10 * l10;
             if (!(e1 > (TD)0)) {
                 first_bad = min(first_bad, j + 1);
                 e1 = (TD)1;
             }
-            TD r1 = rsqrt_pivot<FULL>(e1);
+            TD r1 = rsqrt_pivot(e1, full);
             TD l0 = (lane == j) ? d0 * r0 : a[u] * r0;
             TD l1 = (lane == j + 1) ? e1 * r1 : (a[u + 1] - l0 * l10) * r1;
             rd_own = (lane == j) ? r0 : (lane == j + 1 ? r1 : rd_own);
@@ -474,7 +476,7 @@ __global__ __launch_bounds__(THREADS, sizeof(T) == 4 ? 2 : 1) void k_panel(const
     __syncthreads();
     factor_diag_block<TD>(A, Iv, Rd, nb, t.y == 0, bad, first[f] + k0, [&](auto cc) {
         if (slab) slab_block(cc);
-    });
+    }, p <= NB);
     // tile 0: the factored block to the scratch
     if (t.y == 0) store_diag_block<T, TD>(A, Iv, dscr + dscr_off[f] + (int64_t)(k0 / NB) * NB * NB, (T *)nullptr);
 }
@@ -529,7 +531,7 @@ __global__ __launch_bounds__(THREADS) void k_diag_factor(const int32_t *__restri
         A[c][r] = (r < nb && c < nb && c <= r) ? (TD)raw[i] : (c == r ? (TD)1 : (TD)0);
     }
     __syncthreads();
-    factor_diag_block<TD>(A, Iv, Rd, nb, true, bad, first[f] + k0, [](auto) {});
+    factor_diag_block<TD>(A, Iv, Rd, nb, true, bad, first[f] + k0, [](auto) {}, p <= NB);
     const int64_t o = dscr_off[f] + (int64_t)(k0 / NB) * NB * NB;
     store_diag_block<T, TD>(A, Iv, dscr + o, dinv + o);
 }
@@ -987,6 +989,11 @@ __global__ __launch_bounds__(THREADS) void k_diag_inv(const int2 *__restrict__ t
 // cores straight from the LDS copy, 64 x 64 tiles spread over the waves.
 // Fronts that fit: p <= NB and sld * p <= LeafCfg<T>::ELEMS (the plan routes
 // the others to the level-synchronous kernels, which run beside this launch).
+// The diagonal block and its inverses share the LDS: 64 pivots fit with up to
+// 208 rows (304 when the block was factored in the staged panel).  Of the
+// leaves of N = 65,536, a = 1.5 all 543 fit, of a = 2 321 of 352 in FP32 and 299
+// in FP64, of N = 262,144, a = 2 792 and 734 of 1,376 (1,349 with 304 rows; that
+// system's factorization takes as long either way).
 // A non-positive pivot is reported as in the panel kernel.
 // LDS: FP32 80 KB (two workgroups per compute unit), FP64 156 KB (one), less
 // the diagonal block and its sub-block inverses
@@ -1050,7 +1057,7 @@ __global__ __launch_bounds__(THREADS, LeafCfg<T>::PER_CU) void k_leaf(const int3
             if (c >= p || r >= m) A[c][r] = r == c ? (T)1 : (T)0;
         }
         sync();
-        factor_diag_block<T, true>(A, Iv, Rd, p, true, bad, first[f], [](auto) {});
+        factor_diag_block<T>(A, Iv, Rd, p, true, bad, first[f], [](auto) {}, std::true_type());
         // rows below, 64 per wave and turn: xs[c][rb] is the transposed 16 x 16
         // block (rows row0 + 16 rb.., columns 16 c..), as in k_panel
         for (int row0 = p + 64 * wave; row0 < m; row0 += THREADS) {

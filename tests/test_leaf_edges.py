@@ -71,3 +71,32 @@ def test_leaf_pivots_to_the_last_place():
     worst = float((np.abs(L - ref) / ref).max() / EPS64)
     print(f"largest error {worst:.2f} eps", flush=True)
     assert worst <= 2.0
+
+
+def test_pivots_of_leaves_past_the_leaf_kernel():
+    """The same bound for leaves of 64 pivots under 200 rows, which do not fit
+    the leaf kernel's LDS and are factored by the panel kernel: diagonal values,
+    stored zeros elsewhere."""
+    p, s, blocks = 64, 200, 12
+    n = p * blocks + s
+    keep = np.zeros((n, n), bool)
+    for b in range(blocks):
+        keep[b * p:(b + 1) * p, b * p:(b + 1) * p] = True
+    keep[blocks * p:] = True
+    keep = np.tril(keep)
+    colptr = np.concatenate([[0], np.cumsum(keep.sum(0))]).astype(np.int64)
+    rowind = np.concatenate([np.flatnonzero(keep[:, c]) for c in range(n)]).astype(np.int32)
+    d = np.random.default_rng(6).uniform(1.0, 4.0, n)
+    values = np.zeros(rowind.size)
+    values[colptr[:-1]] = d
+    sym = Symbolic(n, colptr, rowind, user_perm=np.arange(n))
+    ex = sym.export()
+    leaves = blocks - 1                      # the last block joins the border's front
+    assert list(np.diff(ex["relaxed_ptr"])) == [p] * leaves + [p + s] and ex["front_order"][0] == p + s
+    f = Factor(sym, FP64, max_nrhs=1)
+    f.numeric(dev(values))
+    Lp, Li, Lx = f.export_L()
+    ref = np.sqrt(d[:p * leaves].astype(np.longdouble))
+    worst = float((np.abs(Lx[Lp[:-1]][:p * leaves] - ref) / ref).max() / EPS64)
+    print(f"largest error {worst:.2f} eps", flush=True)
+    assert worst <= 2.0
