@@ -898,7 +898,10 @@ template <typename T> struct InvArgs {
 // shares L's array (33 KB of LDS, four workgroups per compute unit): its
 // diagonal sub-blocks replace L's, the blocks below them go to the transposed
 // positions.  (One wave substituting all 64 columns took 22-27 us per launch
-// on the narrow levels, this form 8.)
+// on the narrow levels, this form 8.  Wide levels pay for the 48 idle lanes of
+// the substitution: N = 262,144 FP64, beside the factorization, 2.1 -> 5.2 ms
+// over the 14 levels, of which the diagonal blocks of the super-block inverses
+// are a part; with k_build_xinv 9.0 -> 7.5.)
 template <typename T>
 __global__ __launch_bounds__(THREADS) void k_diag_inv(const int2 *__restrict__ tasks, InvArgs<T> a)
 {

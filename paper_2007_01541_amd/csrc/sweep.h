@@ -14,9 +14,12 @@
 // 65,536 (solve and product) 2.40 -> 0.76 ms.
 //
 // Order and progress: the queue lists every task after all tasks it waits
-// for, and tasks are claimed in queue order, one at a time per workgroup.
-// The first unfinished task therefore always belongs to a running workgroup
-// and waits for nothing, so the launch finishes however few workgroups are
+// for, and tasks are claimed in queue order.  A workgroup runs its tasks in the
+// order it claimed them and holds at most one that it has not started (the
+// short kinds claim their successor first, see run), later in the queue than
+// the one it runs.  The first unfinished task therefore is always being run,
+// not held, and waits for nothing, so the launch finishes however few
+// workgroups are
 // resident.  Every wait is bounded all the same: a workgroup that polls too
 // often raises an abort word, which ends all waits and turns what is
 // published from then on into NaN, and the factor's give-up word, from which
