@@ -19,11 +19,10 @@
 // short kinds claim their successor first, see run), later in the queue than
 // the one it runs.  The first unfinished task therefore is always being run,
 // not held, and waits for nothing, so the launch finishes however few
-// workgroups are
-// resident.  Every wait is bounded all the same: a workgroup that polls too
-// often raises an abort word, which ends all waits and turns what is
-// published from then on into NaN, and the factor's give-up word, from which
-// the host reports it.
+// workgroups are resident.  Every wait is bounded all the same: a workgroup
+// that polls too often raises an abort word, which ends all waits and turns
+// what is published from then on into NaN, and the factor's give-up word, from
+// which the host reports it.
 //
 // Exchanged values are written and read with relaxed device-scope atomics,
 // which are coherent across the eight dies' caches, and a value is its own
