@@ -142,10 +142,21 @@ int kt16_max_rhs()
 // 11.20, 11.04, 10.79 and 10.76 ms; a batch of 32 in FP32 11.13, 11.13,
 // 11.10 and 11.20; N = 262,144 with 64 right-hand sides, FP32 65.5, 65.5,
 // 65.4 and 65.2, FP64 93.1, 93.1, 93.1 and 92.7.
-int32_t late_min_pivots()
+//
+// The solves have levels of their own: the same where that makes their chain
+// of super-blocks shorter than a threshold of LATE_SOLVE pivots does, else that
+// one's (set in the environment, the variable holds for both).  Measured, one
+// solve of 1, 8, 12 and 64 right-hand sides with 1024 over 256 pivots: where the
+// chain gets shorter, N = 16,384, a = 2, 23 -> 21 super-blocks, FP64 1.02, 1.00,
+// 1.07, 1.06; N = 65,536, a = 1.5, 35 -> 33, 0.99, 0.99, 1.04, 1.03; a = 2, 41 ->
+// 39, 1.02, 1.02, 1.03, 1.03; where it does not, N = 65,536, a = 1.2, 0.98, 0.98,
+// 0.99, 0.99 (FP32 0.97, 0.97, 0.99, 0.99), N = 39,322, a = 1.4, FP32 0.95, 0.98,
+// 1.00, 0.99; the factorization gains either way (1.00 to 1.06).
+constexpr int32_t LATE_FACTOR = 256, LATE_SOLVE = 1024;
+int32_t late_min_pivots(int32_t dflt)
 {
     const char *e = std::getenv("WCS_LATE_MIN_PIVOTS");
-    return e ? std::atoi(e) : 256;
+    return e ? std::atoi(e) : dflt;
 }
 
 // Cholesky fronts with at least this many pivots are factored by the fused
@@ -195,15 +206,15 @@ struct SolveLevel {
     std::pair<int64_t, int64_t> below{0, 0};       // backward update-row partial tasks (sbelow_tasks)
     std::pair<int64_t, int64_t> below_sum{0, 0};   // ... and their sums (sbsum_tasks)
     std::vector<SuperStep> bwd;                    // s0 descending
-    std::pair<int64_t, int64_t> xinv{0, 0};        // super-block inverse tasks of this level (xinv_tasks)
 };
 struct Level {
-    SolveLevel sv;
+    SolveLevel sv;                                 // of the solves, whose fronts may be others (see LATE_SOLVE)
     int32_t upd_var = 0;                           // update kernel of this level (WCS_UPD_*; autotuned)
     std::vector<Op> ops;
     std::vector<std::pair<int64_t, int64_t>> ea;   // extend-add rounds into the pivot columns (offset, count)
     std::vector<std::pair<int64_t, int64_t>> ea_post;   // ... into the update matrices, after the trailing updates
     int64_t dinv_off = 0, dinv_cnt = 0;            // diagonal blocks of this level's fronts (dinv_tasks)
+    std::pair<int64_t, int64_t> xinv{0, 0};        // super-block inverse tasks of this level's fronts (xinv_tasks)
     int64_t leaf_off = 0, leaf_cnt = 0;            // fronts factored by the persistent leaf kernel (leaf_queue)
     int64_t fl_off = 0, fl_cnt = 0;                // fronts of this level in flist
 };
@@ -425,18 +436,31 @@ struct Plan {
             ea_split[c] = js;
         }
         int32_t H = S.nlevels;
-        std::vector<std::vector<int32_t>> bylev(H);
-        {
-            // level of every front: its height, or for large fronts one below
-            // its parent's level (parents come after their children)
-            const int32_t late = late_min_pivots();
+        // fronts by level: its height, or for fronts of at least late pivots one
+        // below its parent's level (parents come after their children)
+        auto schedule = [&](int32_t late) {
             std::vector<int32_t> lev(S.height.begin(), S.height.end());
+            std::vector<std::vector<int32_t>> by(H);
             for (int32_t s = ns - 1; s >= 0; s--) {
                 int32_t par = S.sparent[s];
                 if (late > 0 && par > s && pfront[s] >= late) lev[s] = std::max(lev[s], lev[par] - 1);
             }
-            for (int32_t s = 0; s < ns; s++) bylev[lev[s]].push_back(s);
-        }
+            for (int32_t s = 0; s < ns; s++) by[lev[s]].push_back(s);
+            return by;
+        };
+        // super-blocks that a solve passes through one after the other
+        auto chain = [&](const std::vector<std::vector<int32_t>> &by) {
+            int64_t len = 0;
+            for (const std::vector<int32_t> &l : by) {
+                int32_t maxp = 0;
+                for (int32_t s : l) maxp = std::max(maxp, pfront[s]);
+                len += (maxp + SS - 1) / SS;
+            }
+            return len;
+        };
+        const std::vector<std::vector<int32_t>> bylev = schedule(late_min_pivots(LATE_FACTOR));
+        std::vector<std::vector<int32_t>> sbylev = schedule(late_min_pivots(LATE_SOLVE));
+        if (chain(bylev) < chain(sbylev)) sbylev = bylev;
         levels.assign(H, Level());
         flist.clear();
         pan_tasks.clear();
@@ -612,11 +636,31 @@ struct Plan {
         sbwd_tasks.clear();
         sasm_tasks.clear();
         const int32_t step_rows = solve_step_min_rows();
+        // the super-block inverses, with the level that factors the front
+        for (int32_t h = 0; h < H; h++) {
+            std::pair<int64_t, int64_t> &X = levels[h].xinv;
+            X.first = (int64_t)xinv_tasks.size();
+            for (int32_t s : bylev[h]) {
+                if (mfront[s] <= step_rows) continue;
+                int32_t nsup = (pfront[s] + SS - 1) / SS;
+                xoff[s] = xelems;
+                // SS x SS per super-block; the last one only as many 64-column blocks as it
+                // has pivots (no kernel touches the columns beyond)
+                int32_t nb_last = (pfront[s] - (nsup - 1) * SS + SB - 1) / SB;
+                xelems += (int64_t)(nsup - 1) * SS * SS + (int64_t)nb_last * SB * SS;
+                for (int32_t si = 0; si < nsup; si++) {
+                    int32_t nb = (std::min(pfront[s], (si + 1) * SS) - si * SS + SB - 1) / SB;
+                    for (int32_t jb = 0; jb + 1 < nb; jb++)      // the last column block has nothing below its own
+                        for (int32_t q = 0; q < SB / 16; q++) xinv_tasks.push_back(make_int4(s, si, jb, q));
+                }
+            }
+            X.second = (int64_t)xinv_tasks.size() - X.first;
+        }
         for (int32_t h = 0; h < H; h++) {
             SolveLevel &V = levels[h].sv;
             std::vector<int32_t> big;
             V.fused_off = (int64_t)slist.size();
-            for (int32_t s : bylev[h]) {
+            for (int32_t s : sbylev[h]) {
                 if (mfront[s] > step_rows) big.push_back(s);
                 else slist.push_back(s);
             }
@@ -630,21 +674,6 @@ struct Plan {
             for (int32_t s : big)
                 for (int32_t t = 0; t < (mfront[s] + SROWS - 1) / SROWS; t++) sasm_tasks.push_back(make_int2(s, t));
             V.assemble.second = (int64_t)sasm_tasks.size() - V.assemble.first;
-            V.xinv.first = (int64_t)xinv_tasks.size();
-            for (int32_t s : big) {
-                int32_t nsup = (pfront[s] + SS - 1) / SS;
-                xoff[s] = xelems;
-                // SS x SS per super-block; the last one only as many 64-column blocks as it
-                // has pivots (no kernel touches the columns beyond)
-                int32_t nb_last = (pfront[s] - (nsup - 1) * SS + SB - 1) / SB;
-                xelems += (int64_t)(nsup - 1) * SS * SS + (int64_t)nb_last * SB * SS;
-                for (int32_t si = 0; si < nsup; si++) {
-                    int32_t nb = (std::min(pfront[s], (si + 1) * SS) - si * SS + SB - 1) / SB;
-                    for (int32_t jb = 0; jb + 1 < nb; jb++)      // the last column block has nothing below its own
-                        for (int32_t q = 0; q < SB / 16; q++) xinv_tasks.push_back(make_int4(s, si, jb, q));
-                }
-            }
-            V.xinv.second = (int64_t)xinv_tasks.size() - V.xinv.first;
             auto blk_tasks = [&](int32_t s0) {
                 int64_t off = (int64_t)sblk_tasks.size();
                 for (int32_t s : big) {
@@ -695,7 +724,7 @@ struct Plan {
                 V.bwd.push_back({s0, d.first, d.second, off, (int64_t)sbwd_tasks.size() - off});
             }
         }
-        build_sweep(S, bylev);
+        build_sweep(S, sbylev);
         // SpMV chunks of the pivot-order CSR
         spmv_chunks.clear();
         spmv_long.clear();
@@ -1381,7 +1410,7 @@ int launch_factor(wcs_factor f, const double *values, hipStream_t st, Prof *prof
                                 {dinv, f->at<T>(Lo.dinv_u)}, {f->at<T>(Lo.xinv), f->at<T>(Lo.xinv_u)}};
             hipLaunchKernelGGL(k_diag_inv<T>, dim3((unsigned)L.dinv_cnt, nbuf), dim3(THREADS), 0, aux,
                                f->at<int2>(Lo.dinvt) + L.dinv_off, ia);
-            const std::pair<int64_t, int64_t> &xt = L.sv.xinv;
+            const std::pair<int64_t, int64_t> &xt = L.xinv;
             if (xt.second)
                 hipLaunchKernelGGL(k_build_xinv<T>, dim3((unsigned)xt.second, nbuf), dim3(THREADS), 0, aux,
                                    f->at<int4>(Lo.xinvt) + xt.first, ia);

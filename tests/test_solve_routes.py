@@ -79,3 +79,26 @@ def test_super_block_levels_of_few_columns(prec):
             print(f"max_nrhs={hi} prec={prec} part={part} k={k}", flush=True)
             X = f.solve(dev(B[:, :k]), part).cpu().numpy()
             assert np.abs(X - Xo[:, :k]).max() <= tol * np.abs(Xo).max(), (part, k)
+
+
+@pytest.mark.parametrize("kind", ["small", "g6alg", "g5a13"])
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_solve_levels_bitwise(kind, prec, monkeypatch):
+    """The solves' levels of their own (by default those with the shorter chain)
+    against the thresholds 256, 1024 and none for both: the same factor and the
+    same solutions bit for bit, level by level and persistent, whole and half."""
+    m, sym, _ = prepared(*next(c for c in CASES if c[0] == kind))
+    v = dev(m["values"])
+    b = dev(normal_rhs(m["n"], 64, 101))
+    ref = None
+    for late in (None, "256", "1024", "0"):
+        if late is not None:
+            monkeypatch.setenv("WCS_LATE_MIN_PIVOTS", late)
+        f = Factor(sym, prec, max_nrhs=64)
+        f.numeric(v)
+        print(f"{kind} prec={prec} late={late}", flush=True)
+        out = [f.solve(b[:, :k], part) for part in (SOLVE_FULL, SOLVE_L, SOLVE_LT) for k in (1, 8, 12, 64)]
+        if ref is None:
+            ref = f.export_L()[2], out
+        assert np.array_equal(f.export_L()[2], ref[0])
+        assert all(torch.equal(x, y) for x, y in zip(out, ref[1]))
