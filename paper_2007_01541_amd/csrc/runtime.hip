@@ -2255,8 +2255,11 @@ int upload_plan(wcs_factor f, hipStream_t st, wcs_factor *out)
     rc = rc ? rc : upload(f, L.glong, P.glong, st);
     std::vector<int32_t> segp = S.seg_ptr.size() >= 2 ? S.seg_ptr : std::vector<int32_t>{0, S.n};
     rc = rc ? rc : upload(f, L.segp, segp, st);
-    const std::vector<int32_t> status{INT32_MAX, 0};
-    rc = rc ? rc : upload(f, L.bad, status, st);
+    const int32_t status[2] = {INT32_MAX, 0};
+    if (!rc && hipMemcpyAsync(f->ws + L.bad, status, sizeof(status), hipMemcpyHostToDevice, st) != hipSuccess) {
+        set_error("hipMemcpyAsync of the factor's status failed");
+        rc = WCS_EHIP;
+    }
     if (rc == WCS_OK) {
         hipError_t e = hipStreamSynchronize(st);   // host vectors are pageable: finish the copies
         if (e != hipSuccess) {
